@@ -6,11 +6,12 @@
 //   dA = dH * act'(A)                        dW1[i] = X_in[i]^T dA[i]    dX_in[i] = dA[i] W1[i]^T   (Eq. 3)
 //   dS[l,i] = dG[r] on selected pairs, else 0;  dZ[l,:] = S[l,:] * (dS[l,:] - <dS[l,:], S[l,:]>)   (softmax)
 //   dWg = X^T dZ                             dX[l,:] = dZ[l,:] Wg^T + sum_{r: I[r]=l} dX_in[r,:]   (Eq. 2, 3)
-// bf16 with d, d_ff multiples of 64: the four expert products run on the matrix cores (gemm_bf16.h);
-// everything else, and fp32, uses a plain tiled FMA kernel.  Sums over a token's experts run in
+// bf16 with d, d_ff multiples of 64: the four expert products run on bf16 operands (gemm_bf16.h); everything else,
+// and fp32, keeps its intermediates in fp32 and runs on the fp32 matrix instructions (gemm_f32.h).  Sums over a token's experts run in
 // ascending expert order, sums over tokens in fixed split order: no floating-point atomics.
 #include "ec_common.h"
 #include "gemm_bf16.h"
+#include "gemm_f32.h"
 
 namespace ecmoe {
 
@@ -95,104 +96,30 @@ bwd_dz_kernel(const float* __restrict__ S, const float* __restrict__ dG, const i
 }
 
 // ---------------------------------------------------------------------------
-// Plain tiled FMA GEMM, any shape: C[g] = opA(A[g]) . opB(B[g]) (+ epilogue), fp32 accumulation.
+// Products with fp32 intermediates (gemm_f32.h): the whole pass for fp32 tensors and for bf16 widths that the bf16
+// kernel does not cover, the gate products where dZ stays in fp32.  Operands may be stored as bf16.
 //   TRA: A[g] stored [K][M] instead of [M][K];  TRB: B[g] stored [N][K] instead of [K][N].
-//   MULGRAD: C = acc * act'(aux[m][n]).
 // ---------------------------------------------------------------------------
-template <typename TA, typename TB, typename TC, bool TRA, bool TRB, bool MULGRAD, int ACT, typename TAux = TC>
-__global__ void __launch_bounds__(256)
-gemm_plain_kernel(const TA* __restrict__ Ag, const TB* __restrict__ Bg, TC* __restrict__ Cg,
-                  const TAux* __restrict__ auxg, int M, int N, int K, long long sA, long long sB, long long sC) {
-    __shared__ float As[16][64 + 4];  // [k][m]
-    __shared__ float Bs[16][64 + 4];  // [k][n]
-    const int g = blockIdx.z;
-    const TA* A = Ag + (size_t)g * sA;
-    const TB* B = Bg + (size_t)g * sB;
-    TC* C = Cg + (size_t)g * sC;
-    const TAux* aux = MULGRAD ? auxg + (size_t)g * sC : nullptr;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int c = tid; c < 64 * 16; c += 256) {
-            {   // A tile: walk the contiguous axis with consecutive threads
-                const int m = TRA ? (c & 63) : (c >> 4), kk = TRA ? (c >> 6) : (c & 15);
-                const int gm = m0 + m, gk = k0 + kk;
-                float v = 0.0f;
-                if (gm < M && gk < K) v = Cvt<TA>::to_f32(TRA ? A[(size_t)gk * M + gm] : A[(size_t)gm * K + gk]);
-                As[kk][m] = v;
-            }
-            {
-                const int nn = TRB ? (c >> 4) : (c & 63), kk = TRB ? (c & 15) : (c >> 6);
-                const int gn = n0 + nn, gk = k0 + kk;
-                float v = 0.0f;
-                if (gn < N && gk < K) v = Cvt<TB>::to_f32(TRB ? B[(size_t)gn * K + gk] : B[(size_t)gk * N + gn]);
-                Bs[kk][nn] = v;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) { a[q] = As[kk][ty * 4 + q]; b[q] = Bs[kk][tx * 4 + q]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int gm = m0 + ty * 4 + i, gn = n0 + tx * 4 + j;
-            if (gm < M && gn < N) {
-                float v = acc[i][j];
-                if (MULGRAD) {
-                    const float a = Cvt<TAux>::to_f32(aux[(size_t)gm * N + gn]);
-                    float gr = 1.0f;
-                    if (ACT == EC_ACT_RELU) gr = a > 0.0f ? 1.0f : 0.0f;
-                    if (ACT == EC_ACT_GELU) {
-                        const float Phi = 0.5f * (1.0f + erff(a * 0.70710678118654752440f));
-                        gr = Phi + a * 0.39894228040143267794f * expf(-0.5f * a * a);
-                    }
-                    v *= gr;
-                }
-                C[(size_t)gm * N + gn] = Cvt<TC>::from_f32(v);
-            }
-        }
+template <bool TRA, bool TRB, typename TA, typename TB>
+static int product_f32(const TA* A, const TB* B, float* C, int G, int M, int N, int K, long long sA, long long sB,
+                       long long sC, hipStream_t stream, long long k_total = 0) {
+    GemmF32Args<TA, TB, float> p = {};
+    p.A = A; p.B = B; p.C = C;
+    p.M = M; p.N = N; p.K = K; p.G = G;
+    p.sA = sA; p.sB = sB; p.sC = sC; p.k_total = k_total;
+    return gemm_f32<TRA, !TRB, F32_ACT, EC_ACT_IDENTITY>(p, stream);
 }
-
-// grid.y carries the row tiles and grid.z the groups: both are limited to 65535
-static bool plain_grid_ok(int G, int M) { return (M + 63) / 64 <= 65535 && G <= 65535; }
-
-template <typename TA, typename TB, typename TC, bool TRA, bool TRB>
-static int gemm_plain(const TA* A, const TB* B, TC* C, int G, int M, int N, int K, long long sA, long long sB,
-                      long long sC, hipStream_t stream) {
-    if (!plain_grid_ok(G, M)) return EC_ERR_UNSUPPORTED;
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)G);
-    hipLaunchKernelGGL((gemm_plain_kernel<TA, TB, TC, TRA, TRB, false, EC_ACT_IDENTITY>), grid, dim3(256), 0, stream, A, B,
-                       C, (const TC*)nullptr, M, N, K, sA, sB, sC);
-    return EC_OK;
-}
+// dA = (A . B^T) * act'(aux)
 template <typename T>
-static int gemm_plain_mulgrad(const float* A, const T* B, float* C, const T* aux, int G, int M, int N, int K, int act,
-                              hipStream_t stream) {  // A [M][K] fp32, B stored [N][K]
-    if (!plain_grid_ok(G, M)) return EC_ERR_UNSUPPORTED;
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)G);
-    const long long sA = (long long)M * K, sB = (long long)N * K, sC = (long long)M * N;
-    if (act == EC_ACT_RELU)
-        hipLaunchKernelGGL((gemm_plain_kernel<float, T, float, false, true, true, EC_ACT_RELU, T>), grid, dim3(256), 0,
-                           stream, A, B, C, aux, M, N, K, sA, sB, sC);
-    else if (act == EC_ACT_GELU)
-        hipLaunchKernelGGL((gemm_plain_kernel<float, T, float, false, true, true, EC_ACT_GELU, T>), grid, dim3(256), 0,
-                           stream, A, B, C, aux, M, N, K, sA, sB, sC);
-    else
-        hipLaunchKernelGGL((gemm_plain_kernel<float, T, float, false, true, true, EC_ACT_IDENTITY, T>), grid, dim3(256), 0,
-                           stream, A, B, C, aux, M, N, K, sA, sB, sC);
-    return EC_OK;
+static int product_f32_mulgrad(const float* A, const T* B, float* C, const T* aux, int G, int M, int N, int K, int act,
+                               hipStream_t stream) {
+    GemmF32Args<float, T, T> p = {};
+    p.A = A; p.B = B; p.C = C; p.aux = aux;
+    p.M = M; p.N = N; p.K = K; p.G = G;
+    p.sA = (long long)M * K; p.sB = (long long)N * K; p.sC = (long long)M * N;
+    if (act == EC_ACT_RELU) return gemm_f32<false, false, F32_MULGRAD, EC_ACT_RELU>(p, stream);
+    if (act == EC_ACT_GELU) return gemm_f32<false, false, F32_MULGRAD, EC_ACT_GELU>(p, stream);
+    return gemm_f32<false, false, F32_MULGRAD, EC_ACT_IDENTITY>(p, stream);
 }
 
 // Sum of `splits` partial [rows] vectors in split order.
@@ -379,18 +306,18 @@ static int backward_typed(const T* dY, const T* X, const T* Wg, const T* W1, con
         // plain path: every intermediate (dX_e, dA, dX_in) stays in fp32
         const float* dXe = reinterpret_cast<const float*>(base + B.dxe);
         float* dA = reinterpret_cast<float*>(base + B.da);
-        int prc = gemm_plain<T, float, float, true, false>(H, dXe, dW2, Gn, F, D, Mk, (long long)k * d_ff, (long long)k * d,
-                                                           (long long)d_ff * d, stream);
+        int prc = product_f32<true, false>(H, dXe, dW2, Gn, F, D, Mk, (long long)k * d_ff, (long long)k * d,
+                                           (long long)d_ff * d, stream);
         mark();
-        if (prc == EC_OK) prc = gemm_plain_mulgrad<T>(dXe, W2, dA, A, Gn, Mk, F, D, act, stream);
-        mark();
-        if (prc == EC_OK)
-            prc = gemm_plain<T, float, float, true, false>(Xin, dA, dW1, Gn, D, F, Mk, (long long)k * d,
-                                                           (long long)k * d_ff, (long long)d * d_ff, stream);
+        if (prc == EC_OK) prc = product_f32_mulgrad(dXe, W2, dA, A, Gn, Mk, F, D, act, stream);
         mark();
         if (prc == EC_OK)
-            prc = gemm_plain<float, T, float, false, true>(dA, W1, dXin, Gn, Mk, D, F, (long long)k * d_ff,
-                                                           (long long)d * d_ff, (long long)k * d, stream);
+            prc = product_f32<true, false>(Xin, dA, dW1, Gn, D, F, Mk, (long long)k * d, (long long)k * d_ff,
+                                           (long long)d * d_ff, stream);
+        mark();
+        if (prc == EC_OK)
+            prc = product_f32<false, true>(dA, W1, dXin, Gn, Mk, D, F, (long long)k * d_ff, (long long)d * d_ff,
+                                           (long long)k * d, stream);
         mark();
         if (prc != EC_OK) return prc;
     }
@@ -430,27 +357,16 @@ static int backward_typed(const T* dY, const T* X, const T* Wg, const T* W1, con
                                                                                     2 * (int)e, nullptr, 0, stream);
         }
     } else {
-    {   // partial[s] = X[s*len .. ]^T dZ[s*len .. ]   (the last split is shorter; its K is passed per launch)
-        const int full = (int)(n / B.split_len);
-        int prc = EC_OK;
-        if (full > 0)
-            prc = gemm_plain<T, float, float, true, false>(X, dZ, wg_part, full, D, (int)e, (int)B.split_len,
-                                                           (long long)B.split_len * d, (long long)B.split_len * e,
-                                                           (long long)d * e, stream);
-        const int64_t rest = n - (int64_t)full * B.split_len;
-        if (prc == EC_OK && rest > 0)
-            prc = gemm_plain<T, float, float, true, false>(X + (size_t)full * B.split_len * d,
-                                                           dZ + (size_t)full * B.split_len * e,
-                                                           wg_part + (size_t)full * d * e, 1, D, (int)e, (int)rest, 0, 0,
-                                                           0, stream);
+        // partial[s] = X[s*len .. ]^T dZ[s*len .. ], one group per split (the last one may be shorter)
+        int prc = product_f32<true, false>(X, dZ, wg_part, B.splits, D, (int)e, (int)B.split_len, (long long)B.split_len * d,
+                                           (long long)B.split_len * e, (long long)d * e, stream, n);
         if (prc != EC_OK) return prc;
-        long long cnt = (long long)d * e, blocks = (cnt + 255) / 256;
+        const long long cnt = (long long)d * e, blocks = (cnt + 255) / 256;
         hipLaunchKernelGGL(reduce_splits_kernel, dim3((unsigned)(blocks > 4096 ? 4096 : blocks)), dim3(256), 0, stream,
                            wg_part, dWg, cnt, B.splits);
-    }
-    // dXz = dZ Wg^T  (Wg stored [d][e] = [N][K])
-    const int prc = gemm_plain<float, T, float, false, true>(dZ, Wg, dXz, 1, (int)n, D, (int)e, 0, 0, 0, stream);
-    if (prc != EC_OK) return prc;
+        // dXz = dZ Wg^T  (Wg stored [d][e] = [N][K])
+        prc = product_f32<false, true>(dZ, Wg, dXz, 1, (int)n, D, (int)e, 0, 0, 0, stream);
+        if (prc != EC_OK) return prc;
     }
     rc = check_launch();
     if (rc != EC_OK) return rc;

@@ -156,5 +156,13 @@ __device__ __forceinline__ float apply_act(float a) {
     if (ACT == EC_ACT_GELU) return gelu_erf(a);
     return a;
 }
+// d act(a) / da, evaluated in fp32: Phi(a) + a phi(a) for GeLU.
+template <int ACT>
+__device__ __forceinline__ float act_grad(float a) {
+    if (ACT == EC_ACT_RELU) return a > 0.0f ? 1.0f : 0.0f;
+    if (ACT == EC_ACT_GELU)
+        return 0.5f * (1.0f + erff(a * 0.70710678118654752440f)) + a * 0.39894228040143267794f * expf(-0.5f * a * a);
+    return 1.0f;
+}
 
 }  // namespace ecmoe

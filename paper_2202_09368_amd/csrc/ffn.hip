@@ -9,11 +9,12 @@
 //    its fragments come from transposing LDS reads.  Widths that are not
 //    multiples of 64 take a predicated kernel that transposes the weight tile
 //    in registers instead.
-//  * fp32: plain FMA tiles (small parity configuration only).
+//  * fp32: matrix cores too (v_mfma_f32_32x32x2_f32, gemm_f32.h).
 #include <cmath>
 
 #include "ec_common.h"
 #include "gemm_bf16.h"
+#include "gemm_f32.h"
 
 namespace ecmoe {
 
@@ -306,68 +307,17 @@ static int gemm_bf16_dispatch_split(const bf16_t* A, const bf16_t* Alo, const bf
 }
 
 // ===========================================================================
-// fp32 grouped GEMM, 64 x 64 tiles, 4 x 4 outputs per thread.
+// fp32 products (gemm_f32.h): C = act(A.B), optionally the pre-activations too.
 // ===========================================================================
-template <int ACT, bool SAVE_PRE>
-__global__ void __launch_bounds__(256)
-gemm_f32_kernel(const float* __restrict__ Ag, const float* __restrict__ Bg, float* __restrict__ Cg,
-                float* __restrict__ Cpreg, int M, int N, int K) {
-    __shared__ float As[16][64 + 4];  // [k][m]
-    __shared__ float Bs[16][64 + 4];  // [k][n]
-    const int g = blockIdx.z;
-    const float* A = Ag + (size_t)g * M * K;
-    const float* B = Bg + (size_t)g * K * N;
-    float* C = Cg + (size_t)g * M * N;
-    float* Cpre = SAVE_PRE ? Cpreg + (size_t)g * M * N : nullptr;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int c = tid; c < 64 * 16; c += 256) {
-            int m = c >> 4, kk = c & 15;  // A: consecutive threads walk the contraction axis
-            int gm = m0 + m, gk = k0 + kk;
-            As[kk][m] = (gm < M && gk < K) ? A[(size_t)gm * K + gk] : 0.0f;
-            int kb = c >> 6, nn = c & 63;  // B: consecutive threads walk the column axis
-            int gkb = k0 + kb, gn = n0 + nn;
-            Bs[kb][nn] = (gkb < K && gn < N) ? B[(size_t)gkb * N + gn] : 0.0f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) { a[q] = As[kk][ty * 4 + q]; b[q] = Bs[kk][tx * 4 + q]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int gm = m0 + ty * 4 + i, gn = n0 + tx * 4 + j;
-            if (gm < M && gn < N) {
-                if (SAVE_PRE) Cpre[(size_t)gm * N + gn] = acc[i][j];
-                C[(size_t)gm * N + gn] = apply_act<ACT>(acc[i][j]);
-            }
-        }
-}
-
 static int launch_gemm_f32(const float* A, const float* B, float* C, float* Cpre, int G, int M, int N, int K,
-                           int act, hipStream_t stream) {
-    if ((M + 63) / 64 > 65535 || G > 65535) return EC_ERR_UNSUPPORTED;  // grid.y / grid.z limits
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)G), block(256);
-#define EC_SGEMM_CASE(ACTV)                                                                         \
-    if (Cpre) hipLaunchKernelGGL((gemm_f32_kernel<ACTV, true>), grid, block, 0, stream, A, B, C, Cpre, M, N, K); \
-    else hipLaunchKernelGGL((gemm_f32_kernel<ACTV, false>), grid, block, 0, stream, A, B, C, Cpre, M, N, K)
-    if (act == EC_ACT_RELU) { EC_SGEMM_CASE(EC_ACT_RELU); }
-    else if (act == EC_ACT_GELU) { EC_SGEMM_CASE(EC_ACT_GELU); }
-    else { EC_SGEMM_CASE(EC_ACT_IDENTITY); }
-#undef EC_SGEMM_CASE
-    return check_launch();
+                           int act, const int32_t* gather, hipStream_t stream) {
+    GemmF32Args<float, float, float> p = {};
+    p.A = A; p.B = B; p.C = C; p.Cpre = Cpre; p.gather = gather;
+    p.M = M; p.N = N; p.K = K; p.G = G;
+    p.sA = (long long)M * K; p.sB = (long long)K * N; p.sC = (long long)M * N;
+    if (act == EC_ACT_RELU) return gemm_f32<false, true, F32_ACT, EC_ACT_RELU>(p, stream);
+    if (act == EC_ACT_GELU) return gemm_f32<false, true, F32_ACT, EC_ACT_GELU>(p, stream);
+    return gemm_f32<false, true, F32_ACT, EC_ACT_IDENTITY>(p, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -379,6 +329,7 @@ static int launch_gemm_f32(const float* A, const float* B, float* C, float* Cpre
 // (measured: 8192 x 768 tokens, gathered product 99 us against 103 + 13 for the dispatch; 16384 x 1024 tokens,
 // 383 us against 344 + 25).
 bool ffn_can_gather(int dtype, int64_t n, int64_t k, int64_t d, int64_t d_ff) {
+    if (dtype == EC_F32) return n * d * 4 <= ((int64_t)16 << 20);
     return dtype == EC_BF16 && k > 0 && n * d * 2 <= ((int64_t)16 << 20) && gemm_bf16_fast_ok(k, d_ff, d, true, n);
 }
 
@@ -410,12 +361,12 @@ int launch_ffn(const void* Xin, const void* X, const int32_t* I, int64_t n, cons
         return gemm_bf16_dispatch((const bf16_t*)H, (const bf16_t*)W2, (bf16_t*)Xe, nullptr, G, M, (int)d, (int)d_ff,
                                   EC_ACT_IDENTITY, nullptr, 0, stream);
     }
-    if (Xin == nullptr || H_lo != nullptr) return EC_ERR_UNSUPPORTED;
-    int rc = launch_gemm_f32((const float*)Xin, (const float*)W1, (float*)H, (float*)A_save, G, M, (int)d_ff, (int)d, act,
-                             stream);
+    if (H_lo != nullptr) return EC_ERR_UNSUPPORTED;
+    int rc = launch_gemm_f32((const float*)(Xin ? Xin : X), (const float*)W1, (float*)H, (float*)A_save, G, M, (int)d_ff,
+                             (int)d, act, Xin ? nullptr : I, stream);
     if (rc != EC_OK) return rc;
     return launch_gemm_f32((const float*)H, (const float*)W2, (float*)Xe, nullptr, G, M, (int)d, (int)d_ff,
-                           EC_ACT_IDENTITY, stream);
+                           EC_ACT_IDENTITY, nullptr, stream);
 }
 
 }  // namespace ecmoe
