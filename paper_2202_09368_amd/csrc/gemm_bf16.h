@@ -148,37 +148,39 @@ gemm_bf16_kernel(const bf16_t* __restrict__ Aall, const bf16_t* __restrict__ Bal
     // With `gather` (A_MC = false only), row m of group g's left operand is row gather[g*M + m] of one
     // shared [gather_rows, K] matrix: the dispatch of Eq. 3 fused into the tile loads.
     const __amdgpu_buffer_rsrc_t rsrcA = (!A_MC && gather != nullptr)
-        ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Aall), 0, gather_rows * K * 2, 0x00020000)
-        : __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Aall + (size_t)g * M * K), 0, M * K * 2, 0x00020000);
+        ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Aall), 0, (int)(2u * gather_rows * K), 0x00020000)
+        : __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Aall + (size_t)g * M * K), 0, (int)(2u * M * K), 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrcA2 = SPLIT_A
-        ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(X2all + (size_t)g * M * K), 0, M * K * 2, 0x00020000)
+        ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(X2all + (size_t)g * M * K), 0, (int)(2u * M * K), 0x00020000)
         : rsrcA;
     const __amdgpu_buffer_rsrc_t rsrcB = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(Ball + (size_t)g * K * N), 0, K * N * 2, 0x00020000);
+        const_cast<bf16_t*>(Ball + (size_t)g * K * N), 0, (int)(2u * K * N), 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrcB2 = SPLIT_B
-        ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(X2all + (size_t)g * K * N), 0, K * N * 2, 0x00020000)
+        ? __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(X2all + (size_t)g * K * N), 0, (int)(2u * K * N), 0x00020000)
         : rsrcB;
-    const int a_kstep = A_MC ? M * 2 : 2;  // bytes per unit of k in the scalar stage offset
-    const int b_kstep = B_KC ? 2 : N * 2;
+    const unsigned int a_kstep = A_MC ? M * 2 : 2;  // bytes per unit of k in the scalar stage offset
+    const unsigned int b_kstep = B_KC ? 2 : N * 2;
 
     // Per-thread byte offsets inside the group's matrices (the stage offset is added as a scalar) and
     // element offsets inside an LDS stage.  Every load instruction covers whole contiguous row pieces.
-    int a_voff[A_CHUNKS], a_lds[A_CHUNKS], b_voff[B_CHUNKS], b_lds[B_CHUNKS];
+    // Byte offsets are unsigned: a group's matrix may take up to 4 GiB.
+    unsigned int a_voff[A_CHUNKS], b_voff[B_CHUNKS];
+    int a_lds[A_CHUNKS], b_lds[B_CHUNKS];
 #pragma unroll
     for (int r = 0; r < A_CHUNKS; ++r) {
         const int c = tid + 256 * r;
         if (A_MC) {
             const int krow = c / (BM / 8), ch = c % (BM / 8);
-            a_voff[r] = (krow * M + m0 + ch * 8) * 2;
+            a_voff[r] = ((unsigned)krow * M + m0 + ch * 8) * 2u;
             a_lds[r] = krow * A_PITCH + ch * 8;
         } else {
             const int row = c >> 3, kch = c & 7;
             if (gather != nullptr) {
                 const int gm = m0 + row;  // rows past M and empty rows (index -1) point outside the buffer: zeros
                 const int src = gm < M ? gather[(size_t)g * M + gm] : -1;
-                a_voff[r] = src >= 0 ? (src * K + kch * 8) * 2 : 0x7FFFFF00;
+                a_voff[r] = src >= 0 ? ((unsigned)src * K + kch * 8) * 2u : 0x7FFFFF00u;
             } else {
-                a_voff[r] = ((m0 + row) * K + kch * 8) * 2;
+                a_voff[r] = ((unsigned)(m0 + row) * K + kch * 8) * 2u;
             }
             a_lds[r] = row * A_PITCH + kch * 8;
         }
@@ -188,11 +190,11 @@ gemm_bf16_kernel(const bf16_t* __restrict__ Aall, const bf16_t* __restrict__ Bal
         const int c = tid + 256 * r;
         if (B_KC) {
             const int row = c >> 3, kch = c & 7;
-            b_voff[r] = ((n0 + row) * K + kch * 8) * 2;
+            b_voff[r] = ((unsigned)(n0 + row) * K + kch * 8) * 2u;
             b_lds[r] = A_ELEMS + row * B_PITCH + kch * 8;
         } else {
             const int krow = c / (BN / 8), ch = c % (BN / 8);
-            b_voff[r] = (krow * N + n0 + ch * 8) * 2;
+            b_voff[r] = ((unsigned)krow * N + n0 + ch * 8) * 2u;
             b_lds[r] = A_ELEMS + krow * B_PITCH + ch * 8;
         }
     }
@@ -598,8 +600,8 @@ constexpr size_t gemm_bf16_lds_bytes() {
 }
 
 // True when the kernel covers the shape (otherwise callers fall back or refuse).  A contraction-
-// contiguous operand needs K % 64 == 0 (the tail of a row would run into the next row); operands that
-// keep k as the row index are zero-filled past K by the buffer range check.
+// contiguous operand needs K % 64 == 0 (the tail of a row would run into the next row) unless the other operand keeps k
+// as its row index: that kind is zero-filled past K by the buffer range check.
 inline bool gemm_bf16_shape_ok(int64_t M, int64_t N, int64_t K, bool k_contiguous_operand = true,
                                bool m_contiguous_operand = false) {
     return (!k_contiguous_operand || (K % GEMM_BK) == 0) && (N % 8) == 0 && (!m_contiguous_operand || (M % 8) == 0) &&
