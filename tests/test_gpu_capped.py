@@ -167,3 +167,49 @@ def test_capped_backward(m, ref, base, kw, b, tol):
         err = max_rel_err(to_host(got), g[key])
         _p(f"[capped backward] {key} max rel err {err:.3e}")
         assert err <= tol
+
+
+@pytest.mark.parametrize("n,e", [
+    (37, 1), (2500, 8), (5000, 7), (12000, 3), (70, 9), (2500, 16), (5000, 12), (12000, 16), (100, 17), (2500, 32),
+    (5000, 20), (100, 40), (2500, 64), (300, 100), (8200, 128),     # every form of the one-launch solver, with remainders
+    (100, 130),                                                     # more experts than it holds: two launches per sweep
+])
+def test_capped_solver_forms(m, ref, n, e):
+    S_h = _scores(n, e, n * e, 0.3)
+    k, b, lam, iters = max(1, 2 * n // e) if e > 1 else n // 2, 2.0, 3e-3, 30
+    St = to_dev(np.ascontiguousarray(S_h.T))
+    ws = torch.empty(m.ec_moe_capped_workspace_bytes(n, e), dtype=torch.uint8, device="cuda")
+    A = torch.full((e, n), float("nan"), dtype=torch.float32, device="cuda")
+    m.ec_moe_capped_assignment(St, k, b, lam, iters, A, ws)
+    torch.cuda.synchronize()
+    A_o = ref.capped_assignment(S_h, k, b, lam, iters)
+    assert np.abs(to_host(A).astype(np.float64) - A_o.astype(np.float64)).max() <= A_TOL
+
+
+def test_capped_streams_and_capture(m):
+    """Solvers on several streams take turns; inside a capture the per-sweep launches run, with the same result."""
+    n, e, k = 3000, 16, 300
+    sides = []
+    for s in range(4):
+        St = to_dev(np.ascontiguousarray(_scores(n, e, s, 0.3).T))
+        ws = torch.empty(m.ec_moe_capped_workspace_bytes(n, e), dtype=torch.uint8, device="cuda")
+        sides.append((St, ws, torch.empty((e, n), device="cuda"), torch.empty((e, n), device="cuda"), torch.cuda.Stream()))
+    for St, ws, A, _, _ in sides:
+        m.ec_moe_capped_assignment(St, k, 2.0, 1e-3, 40, A, ws)
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for St, ws, _, A, stream in sides:
+            with torch.cuda.stream(stream):
+                m.ec_moe_capped_assignment(St, k, 2.0, 1e-3, 40, A, ws)
+    torch.cuda.synchronize()
+    for _, _, A, A2, _ in sides:
+        assert torch.equal(A, A2)
+    St, ws, A, A2, _ = sides[0]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        m.ec_moe_capped_assignment(St, k, 2.0, 1e-3, 40, A2, ws)
+    for _ in range(3):
+        A2.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (A2 - A).abs().max().item() <= A_TOL
