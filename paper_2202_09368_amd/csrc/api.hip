@@ -30,10 +30,7 @@ WsLayout ws_layout(int64_t n, int64_t d, int64_t e, int64_t k, int64_t d_ff, int
     L.h_lo = take(hilo ? (size_t)e * k * (size_t)(d_ff > 0 ? d_ff : 0) * 2 : 0);
     L.xe32 = take(hilo ? (size_t)e * k * d * 4 : 0);
     L.bitmap = take((size_t)n * (size_t)ceil_div(e, 32) * 4);
-    L.offsets = take((size_t)(n + 1) * 4);
-    L.inv = take((size_t)e * k * 4);
-    L.slot_cnt = take((size_t)n * 4);
-    L.slots = take((size_t)n * COMBINE_SLOT_CAP * 4);
+    L.pos = take((size_t)n * e * 4);
     L.choice = take((size_t)n * 8 * 4);
     L.bwd = off;
     if (with_backward) take(bwd_ws_bytes(n, d, e, k, d_ff, dtype, hilo));
@@ -65,16 +62,8 @@ static bool ws_ok(const void* ws, size_t ws_bytes, size_t need) {
 }
 static unsigned char* at(void* ws, size_t off) { return static_cast<unsigned char*>(ws) + off; }
 
-CombineIndex combine_index_at(void* ws, const WsLayout& L, int64_t e) {
-    CombineIndex ix;
-    ix.use_slots = e <= COMBINE_SLOT_CAP;
-    ix.slot_cap = e <= 4 ? 4 : e <= 8 ? 8 : 16;
-    ix.slot_cnt = (int32_t*)at(ws, L.slot_cnt);
-    ix.slots = (int32_t*)at(ws, L.slots);
-    ix.bitmap = (uint32_t*)at(ws, L.bitmap);
-    ix.offsets = (int32_t*)at(ws, L.offsets);
-    ix.inv = (int32_t*)at(ws, L.inv);
-    return ix;
+CombineIndex combine_index_at(void* ws, const WsLayout& L) {
+    return {(uint32_t*)at(ws, L.bitmap), (int32_t*)at(ws, L.pos), nullptr, nullptr, nullptr};
 }
 
 }  // namespace ecmoe
@@ -112,7 +101,7 @@ int ec_moe_topk_tokens(const float* St, int64_t n, int64_t e, int64_t k, float* 
                        size_t ws_bytes, void* stream) {
     if (!St || !G || !I || !sizes_ok(n, 1, e, k) || !all_aligned(St, G, I)) return EC_ERR_INVALID_ARG;
     (void)ws; (void)ws_bytes;  // the selection needs no scratch in global memory
-    return launch_topk(St, n, e, k, G, I, nullptr, nullptr, 0, nullptr, (hipStream_t)stream);
+    return launch_topk(St, n, e, k, G, I, nullptr, (hipStream_t)stream);
 }
 
 int ec_moe_topk_tokens_grouped(const float* St, int64_t n, int64_t e, int64_t groups, int64_t k_g, float* G,
@@ -122,7 +111,7 @@ int ec_moe_topk_tokens_grouped(const float* St, int64_t n, int64_t e, int64_t gr
         !all_aligned(St, G, I))
         return EC_ERR_INVALID_ARG;
     (void)ws; (void)ws_bytes;
-    return launch_topk(St, n, e, k_g, G, I, nullptr, nullptr, 0, nullptr, (hipStream_t)stream, groups);
+    return launch_topk(St, n, e, k_g, G, I, nullptr, (hipStream_t)stream, groups);
 }
 
 int ec_moe_dispatch(const void* X, const int32_t* I, void* Xin, int64_t n, int64_t d, int64_t e, int64_t k,
@@ -168,12 +157,9 @@ int ec_moe_combine(const void* Xe, const float* G, const int32_t* I, void* Xout,
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t a = off; off = align_up(off + bytes, 256); return a; };
     L.bitmap = take((size_t)n * (size_t)ceil_div(e, 32) * 4);
-    L.offsets = take((size_t)(n + 1) * 4);
-    L.inv = take((size_t)e * k * 4);
-    L.slot_cnt = take((size_t)n * 4);
-    L.slots = take((size_t)n * COMBINE_SLOT_CAP * 4);
+    L.pos = take((size_t)n * e * 4);
     if (!ws_ok(ws, ws_bytes, off)) return EC_ERR_WORKSPACE;
-    const CombineIndex ix = combine_index_at(ws, L, e);
+    const CombineIndex ix = combine_index_at(ws, L);
     int rc = launch_combine_index(I, n, e, k, ix, (hipStream_t)stream);
     if (rc != EC_OK) return rc;
     return launch_combine(Xe, G, I, Xout, n, d, e, k, dtype, ix, (hipStream_t)stream);
@@ -200,7 +186,7 @@ static int experts_then_combine(const void* Xin, const void* X, const int32_t* I
         float* Xe32 = (float*)at(ws, L.xe32);
         int rc = launch_ffn(Xin, X, I, n, W1, W2, Xe_out, A_out, H, e, k, d, d_ff, act, dtype, st, at(ws, L.h_lo), Xe32);
         if (rc != EC_OK) return rc;
-        return launch_combine(Xe32, G, I, Xout, n, d, e, k, dtype, ix, st, nullptr, false, nullptr, true);
+        return launch_combine(Xe32, G, I, Xout, n, d, e, k, dtype, ix, st, nullptr, nullptr, true);
     }
     void* Xe = Xe_out ? Xe_out : at(ws, L.xe);
     int rc = launch_ffn(Xin, X, I, n, W1, W2, Xe, A_out, H, e, k, d, d_ff, act, dtype, st);
@@ -241,11 +227,10 @@ static int forward_impl(const void* X, const void* Wg, const void* W1, const voi
     int32_t* I = I_out ? I_out : (int32_t*)at(ws, L.i);
     void* Xin = Xin_out ? Xin_out : at(ws, L.xin);
 
-    const CombineIndex ix = combine_index_at(ws, L, e);
-    int rc = launch_gate(X, Wg, S_out, St, n, d, e, dtype, combine_zero_ptr(ix), combine_zero_words(ix, n, e), st);
+    const CombineIndex ix = combine_index_at(ws, L);
+    int rc = launch_gate(X, Wg, S_out, St, n, d, e, dtype, ix.bitmap, combine_zero_words(n, e), st);
     if (rc != EC_OK) return rc;
-    rc = launch_topk(St, n, e, k_g, G, I, ix.use_slots ? ix.slot_cnt : nullptr, ix.slots, ix.slot_cap,
-                     ix.use_slots ? nullptr : ix.bitmap, st, groups);
+    rc = launch_topk(St, n, e, k_g, G, I, &ix, st, groups);
     if (rc != EC_OK) return rc;
     // The bucket gather is fused into the first expert product unless the caller wants X_in itself.  With
     // identity experts X_e = X_in = the gathered rows of X: unless the caller asks for one of them, the
@@ -253,7 +238,7 @@ static int forward_impl(const void* X, const void* Wg, const void* W1, const voi
     const bool fused_gather = !identity && Xin_out == nullptr && ffn_can_gather(dtype, n, k, d, d_ff);
     if (identity) {
         void* rows = Xin_out ? Xin_out : Xe_out;
-        if (rows == nullptr) return launch_combine(X, G, I, Xout, n, d, e, k, dtype, ix, st, nullptr, false, I);
+        if (rows == nullptr) return launch_combine(X, G, I, Xout, n, d, e, k, dtype, ix, st, nullptr, I);
         rc = launch_dispatch(X, I, rows, n, d, e, k, dtype, st);
         if (rc != EC_OK) return rc;
         if (Xin_out && Xe_out) {
@@ -292,8 +277,7 @@ int ec_moe_token_choice(const float* S, int64_t n, int64_t e, int64_t m, int64_t
         m > 8 || cap < 1 || cap > n || e * cap >= (int64_t)1 << 31 || !all_aligned(S, G, I, load))
         return EC_ERR_INVALID_ARG;
     if (!ws_ok(ws, ws_bytes, (size_t)n * 8 * 4)) return EC_ERR_WORKSPACE;
-    return launch_token_choice(S, n, e, m, cap, G, I, load, (int32_t*)ws, nullptr, nullptr, 0, nullptr,
-                               (hipStream_t)stream);
+    return launch_token_choice(S, n, e, m, cap, G, I, load, (int32_t*)ws, nullptr, (hipStream_t)stream);
 }
 
 int ec_moe_forward_token_choice(const void* X, const void* Wg, const void* W1, const void* W2, double c, int64_t m,
@@ -326,12 +310,10 @@ int ec_moe_forward_token_choice(const void* X, const void* Wg, const void* W1, c
     int32_t* I = I_out ? I_out : (int32_t*)at(ws, L.i);
     void* Xin = Xin_out ? Xin_out : at(ws, L.xin);
 
-    const CombineIndex ix = combine_index_at(ws, L, e);
-    int rc = launch_gate(X, Wg, S, nullptr, n, d, e, dtype, combine_zero_ptr(ix), combine_zero_words(ix, n, e), st);
+    const CombineIndex ix = combine_index_at(ws, L);
+    int rc = launch_gate(X, Wg, S, nullptr, n, d, e, dtype, ix.bitmap, combine_zero_words(n, e), st);
     if (rc != EC_OK) return rc;
-    rc = launch_token_choice(S, n, e, m, k, G, I, load_out, (int32_t*)at(ws, L.choice),
-                             ix.use_slots ? ix.slot_cnt : nullptr, ix.slots, ix.slot_cap,
-                             ix.use_slots ? nullptr : ix.bitmap, st);
+    rc = launch_token_choice(S, n, e, m, k, G, I, load_out, (int32_t*)at(ws, L.choice), &ix, st);
     if (rc != EC_OK) return rc;
     const bool fused_gather = !identity && Xin_out == nullptr && ffn_can_gather(dtype, n, k, d, d_ff);
     if (!fused_gather) {
@@ -394,16 +376,13 @@ int ec_moe_forward_capped(const void* X, const void* Wg, const void* W1, const v
     void* solver = at(ws, L.total);
     float* A = A_out ? A_out : (float*)at(ws, L.total + capped_ws_bytes(n, e));
 
-    const CombineIndex ix = combine_index_at(ws, L, e);
-    int rc = launch_gate(X, Wg, S_out, St, n, d, e, dtype, combine_zero_ptr(ix), combine_zero_words(ix, n, e), st);
+    const CombineIndex ix = combine_index_at(ws, L);
+    int rc = launch_gate(X, Wg, S_out, St, n, d, e, dtype, ix.bitmap, combine_zero_words(n, e), st);
     if (rc != EC_OK) return rc;
     rc = launch_capped_assignment(St, n, e, k, b, lambda, iters, A, solver, st);
     if (rc != EC_OK) return rc;
-    // indices from TopK(A, k); the values it returns are entries of A and are replaced by the scores
-    rc = launch_topk(A, n, e, k, G, I, ix.use_slots ? ix.slot_cnt : nullptr, ix.slots, ix.slot_cap,
-                     ix.use_slots ? nullptr : ix.bitmap, st);
-    if (rc != EC_OK) return rc;
-    rc = launch_gather_scores(St, I, G, n, e, k, st);
+    // indices from TopK(A, k), weights from the scores
+    rc = launch_topk(A, n, e, k, G, I, &ix, st, 1, St);
     if (rc != EC_OK) return rc;
     const bool fused_gather = !identity && ffn_can_gather(dtype, n, k, d, d_ff);
     if (!fused_gather) {

@@ -22,7 +22,9 @@ template <typename T, int VEC, typename TOut>
 __global__ void __launch_bounds__(256)
 bwd_rows_kernel(const T* __restrict__ dY, const T* __restrict__ Xe, const float* __restrict__ G,
                 const int32_t* __restrict__ I, TOut* __restrict__ dXe, float* __restrict__ dG, long long rows, int d,
-                TOut* __restrict__ dXe_lo) {  // dXe_lo (optional): G dY - dXe, what the rounding of dXe dropped
+                TOut* __restrict__ dXe_lo,  // (optional) G dY - dXe, what the rounding of dXe dropped
+                uint32_t* __restrict__ zero_buf, long long zero_words) {  // cleared on the way: the bitmap of the index
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < zero_words; i += (long long)gridDim.x * 256) zero_buf[i] = 0u;
     typedef T vec_t __attribute__((ext_vector_type(VEC)));  // VEC elements = 16 bytes when the rows allow it
     typedef TOut ovec_t __attribute__((ext_vector_type(VEC)));
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -54,44 +56,40 @@ bwd_rows_kernel(const T* __restrict__ dY, const T* __restrict__ Xe, const float*
 }
 
 // ---------------------------------------------------------------------------
-// Softmax backward per token (one wavefront per token).  The token's selected pairs come from its
-// expert-ascending row list; dZ is written densely as fp32 [n,e] and, optionally, as bf16.
+// Softmax backward per token (one wavefront per token).  The token's selected pairs come from the dense
+// token-major index; dZ is written densely as fp32 [n,e] and, optionally, as bf16.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
-bwd_dz_kernel(const float* __restrict__ S, const float* __restrict__ dG, const int32_t* __restrict__ offsets,
-              const int32_t* __restrict__ inv, float* __restrict__ dZ, bf16_t* __restrict__ dZb, int n, int e, int k) {
-    __shared__ float ds[4][EC_MOE_MAX_EXPERTS];
+bwd_dz_kernel(const float* __restrict__ S, const float* __restrict__ dG, const uint32_t* __restrict__ bitmap,
+              const int32_t* __restrict__ pos, float* __restrict__ dZ, bf16_t* __restrict__ dZb, int n, int e) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int base = blockIdx.x * 4; base < n; base += gridDim.x * 4) {
-        const int l = base + wave;
-        const bool active = l < n;
-        for (int i = lane; i < e; i += kWave) ds[wave][i] = 0.0f;
-        __syncthreads();
-        float dot = 0.0f;
-        if (active) {
-            const int beg = offsets[l], end = offsets[l + 1];
-            for (int p = beg + lane; p < end; p += kWave) {
-                const int r = inv[p];
-                const int i = r / k;
-                const float v = dG[r];
-                ds[wave][i] = v;  // a token appears at most once per expert
-                dot = fmaf(v, S[(size_t)l * e + i], dot);
-            }
+    const int words = (e + 31) >> 5;
+    for (int l = blockIdx.x * 4 + wave; l < n; l += gridDim.x * 4) {
+        float dot = 0.0f, s0 = 0.0f, v0 = 0.0f;  // s0, v0: this lane's first expert, all of them up to 64 experts
+        auto pair = [&](int i, float& s, float& v) {
+            const bool on = (bitmap[(size_t)l * words + (i >> 5)] >> (i & 31)) & 1u;
+            s = S[(size_t)l * e + i];
+            v = on ? dG[pos[(size_t)l * e + i]] : 0.0f;
+        };
+        if (lane < e) pair(lane, s0, v0);
+        dot = s0 * v0;
+        for (int i = lane + kWave; i < e; i += kWave) {
+            float s, v;
+            pair(i, s, v);
+            dot = fmaf(v, s, dot);
         }
         dot = wave_reduce_sum(dot);
-        __syncthreads();
-        if (active) {
-            for (int i = lane; i < e; i += kWave) {
-                const float z = S[(size_t)l * e + i] * (ds[wave][i] - dot);
-                dZ[(size_t)l * e + i] = z;
-                if (dZb != nullptr) {  // z = hi + lo with both in bf16 (error 2^-17 |z|), row layout [hi(e) | lo(e)]
-                    const bf16_t hi = static_cast<bf16_t>(z);
-                    dZb[(size_t)l * 2 * e + i] = hi;
-                    dZb[(size_t)l * 2 * e + e + i] = static_cast<bf16_t>(z - static_cast<float>(hi));
-                }
+        for (int i = lane; i < e; i += kWave) {
+            float s = s0, v = v0;
+            if (i != lane) pair(i, s, v);
+            const float z = s * (v - dot);
+            dZ[(size_t)l * e + i] = z;
+            if (dZb != nullptr) {  // z = hi + lo with both in bf16 (error 2^-17 |z|), row layout [hi(e) | lo(e)]
+                const bf16_t hi = static_cast<bf16_t>(z);
+                dZb[(size_t)l * 2 * e + i] = hi;
+                dZb[(size_t)l * 2 * e + e + i] = static_cast<bf16_t>(z - static_cast<float>(hi));
             }
         }
-        __syncthreads();
     }
 }
 
@@ -236,6 +234,9 @@ static int backward_typed(const T* dY, const T* X, const T* Wg, const T* W1, con
                            gemm_bf16_shape_ok(d, 2 * e, B.split_len, false, true) && gemm_bf16_shape_ok(n, d, 2 * e);
     bf16_t* Wg2 = reinterpret_cast<bf16_t*>(base + B.wg2);
 
+    const CombineIndex ix = combine_index_at(ws, L);
+    const long long zero_words = combine_zero_words(n, e);
+
     // Eq. 4 backwards: dX_e, dG (dX_e in bf16 as a matrix-core operand, in fp32 on the plain path)
     {
         long long blocks = ceil_div(rows, 4);
@@ -247,17 +248,17 @@ static int backward_typed(const T* dY, const T* X, const T* Wg, const T* W1, con
             T* dXe_lo = hilo ? reinterpret_cast<T*>(base + B.dxe_lo) : nullptr;
             if (d % V16 == 0)
                 hipLaunchKernelGGL((bwd_rows_kernel<T, V16, T>), grid, block, 0, stream, dY, Xe, G, I, (T*)dXe, dG, rows, D,
-                                   dXe_lo);
+                                   dXe_lo, ix.bitmap, zero_words);
             else
                 hipLaunchKernelGGL((bwd_rows_kernel<T, 1, T>), grid, block, 0, stream, dY, Xe, G, I, (T*)dXe, dG, rows, D,
-                                   dXe_lo);
+                                   dXe_lo, ix.bitmap, zero_words);
         } else {
             if (d % V16 == 0)
                 hipLaunchKernelGGL((bwd_rows_kernel<T, V16, float>), grid, block, 0, stream, dY, Xe, G, I, (float*)dXe, dG,
-                                   rows, D, (float*)nullptr);
+                                   rows, D, (float*)nullptr, ix.bitmap, zero_words);
             else
                 hipLaunchKernelGGL((bwd_rows_kernel<T, 1, float>), grid, block, 0, stream, dY, Xe, G, I, (float*)dXe, dG,
-                                   rows, D, (float*)nullptr);
+                                   rows, D, (float*)nullptr, ix.bitmap, zero_words);
         }
     }
     mark();  // 0: rows
@@ -324,12 +325,8 @@ static int backward_typed(const T* dY, const T* X, const T* Wg, const T* W1, con
     int rc = check_launch();
     if (rc != EC_OK) return rc;
 
-    // token-major row lists (CSR form, expert-ascending) rebuilt from I
-    CombineIndex ix = combine_index_at(ws, L, e);
-    ix.use_slots = false;
-    rc = launch_combine_index(I, n, e, k, ix, stream);
-    if (rc != EC_OK) return rc;
-    rc = launch_combine_csr(I, n, e, k, ix, stream);
+    // token-major index rebuilt from I
+    rc = launch_combine_index(I, n, e, k, ix, stream, true);
     if (rc != EC_OK) return rc;
     mark();  // 5: token-major index
 
@@ -337,8 +334,8 @@ static int backward_typed(const T* dY, const T* X, const T* Wg, const T* W1, con
     {
         long long blocks = ceil_div(n, 4);
         if (blocks > 65536) blocks = 65536;
-        hipLaunchKernelGGL(bwd_dz_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, S, dG, ix.offsets, ix.inv, dZ,
-                           mfma_gate ? dZb : (bf16_t*)nullptr, (int)n, (int)e, (int)k);
+        hipLaunchKernelGGL(bwd_dz_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, S, dG, ix.bitmap, ix.pos, dZ,
+                           mfma_gate ? dZb : (bf16_t*)nullptr, (int)n, (int)e);
     }
     mark();  // 6: dZ
     if (mfma_gate) {
@@ -372,7 +369,7 @@ static int backward_typed(const T* dY, const T* X, const T* Wg, const T* W1, con
     if (rc != EC_OK) return rc;
     mark();  // 7: gate products (dWg, dZ Wg^T)
     // dX = dXz + scatter-add of dX_in rows, expert-ascending, rounded once
-    rc = launch_combine(dXin, nullptr, I, dX, n, d, e, k, dtype, ix, stream, dXz, true, nullptr, BF);
+    rc = launch_combine(dXin, nullptr, I, dX, n, d, e, k, dtype, ix, stream, dXz, nullptr, BF);
     mark();  // 8: scatter into dX
     return rc;
 }

@@ -400,14 +400,6 @@ capped_exp_kernel(const double* __restrict__ logA, float* __restrict__ A, long l
         A[i] = (float)exp(logA[i]);
 }
 
-// G[i,j] = St[i, I[i,j]]: the gate weights stay the scores, only the indices come from A.
-__global__ void __launch_bounds__(256)
-gather_scores_kernel(const float* __restrict__ St, const int32_t* __restrict__ I, float* __restrict__ G,
-                     long long rows, int k, int n) {
-    for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < rows; q += (long long)gridDim.x * 256)
-        G[q] = St[(size_t)(q / k) * n + I[q]];
-}
-
 size_t capped_ws_bytes(int64_t n, int64_t e) {
     return 2 * align_up((size_t)e * n * 8, 256) + align_up((size_t)n * 8, 256) + align_up((size_t)e * 8, 256);
 }
@@ -462,13 +454,6 @@ int launch_capped_assignment(const float* St, int64_t n, int64_t e, int64_t k, d
                            r, (int)n, (int)e, log_b);
     }
     hipLaunchKernelGGL(capped_exp_kernel, dim3(grid_for(count)), dim3(256), 0, stream, logA, A, count);
-    return check_launch();
-}
-
-int launch_gather_scores(const float* St, const int32_t* I, float* G, int64_t n, int64_t e, int64_t k,
-                         hipStream_t stream) {
-    const long long rows = (long long)e * k;
-    hipLaunchKernelGGL(gather_scores_kernel, dim3(grid_for(rows)), dim3(256), 0, stream, St, I, G, rows, (int)k, (int)n);
     return check_launch();
 }
 

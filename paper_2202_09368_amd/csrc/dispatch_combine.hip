@@ -71,34 +71,22 @@ int launch_dispatch(const void* X, const int32_t* I, void* Xin, int64_t n, int64
 }
 
 // ------------------------------------------------------------------- combine
-// Token-major index of the routing, two forms:
-//  * slot lists (e <= COMBINE_SLOT_CAP): slot_cnt[l] experts chose token l and left their bucket rows
-//    in slots[l*cap ...] in arrival order; the combine kernel visits them in ascending row order,
-//    which is ascending expert order because an expert holds a token at most once.
-//  * CSR (any e): bitmap[l] has one bit per expert, offsets = exclusive scan of its popcounts,
-//    inv[offsets[l] + (number of set bits below i)] = i*k + j -- already expert-ascending.
-// Both are built with integer atomics only (OR / counting), so the result never depends on timing.
+// Token-major index of the routing (CombineIndex), built with integer stores and ORs only, so it never depends on
+// timing.  Lists of the other form: offsets = exclusive scan of the bitmap's popcounts,
+// inv[offsets[l] + (number of set bits below i)] = i*k + j -- expert-ascending.
 __global__ void __launch_bounds__(256)
 fill_u32_kernel(uint32_t* __restrict__ p, long long count, uint32_t v) {
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < count; i += (long long)gridDim.x * 256) p[i] = v;
 }
 
 __global__ void __launch_bounds__(256)
-bitmap_kernel(const int32_t* __restrict__ I, uint32_t* __restrict__ bitmap, long long rows, int k, int words) {
+index_kernel(const int32_t* __restrict__ I, uint32_t* __restrict__ bitmap, int32_t* __restrict__ pos, long long rows, int k,
+             int words, int e) {
     for (long long r = (long long)blockIdx.x * 256 + threadIdx.x; r < rows; r += (long long)gridDim.x * 256) {
-        int i = (int)(r / k);
-        if (I[r] >= 0) atomicOr(&bitmap[(size_t)I[r] * words + (i >> 5)], 1u << (i & 31));  // -1: empty row
-    }
-}
-
-__global__ void __launch_bounds__(256)
-slots_kernel(const int32_t* __restrict__ I, int32_t* __restrict__ slot_cnt, int32_t* __restrict__ slots,
-             long long rows, int cap) {
-    for (long long r = (long long)blockIdx.x * 256 + threadIdx.x; r < rows; r += (long long)gridDim.x * 256) {
-        const int l = I[r];
+        const int i = (int)(r / k), l = I[r];
         if (l < 0) continue;  // empty buffer row
-        const int s = atomicAdd(&slot_cnt[l], 1);
-        if (s < cap) slots[(size_t)l * cap + s] = (int32_t)r;
+        if (pos != nullptr) pos[(size_t)l * e + i] = (int32_t)r;
+        atomicOr(&bitmap[(size_t)l * words + (i >> 5)], 1u << (i & 31));
     }
 }
 
@@ -186,138 +174,108 @@ inverse_index_kernel(const int32_t* __restrict__ I, const uint32_t* __restrict__
     }
 }
 
-// A block works on runs of `chunk` (at most COMBINE_CHUNK) consecutive tokens.  Phase 1 resolves the index of the whole run at once:
-// the run's list entries (bucket row -> source row and weight) go to LDS, so the chain offsets -> list -> weight
-// is waited for once per run and not once per token.  Phase 2 streams the rows: one token per group of `tpr`
-// threads, each thread owning 16 bytes of the row (8 bf16 / 4 fp32) per step and accumulating in fp32, with
-// nothing but the row loads left to wait for.  CAP = 0: entries come from the CSR lists (expert-ascending).
-// CAP > 0: from the token's slot list (capacity CAP), put in ascending row order by repeated minimum -- the
-// lists are short, the capacity factor on average.  A run with more than COMBINE_ENTRIES entries (tokens that
-// many experts chose) reads its index from memory entry by entry instead.  The order of the additions of a
-// token is the order of its list in every case.
-constexpr int COMBINE_CHUNK = 32;
-constexpr int COMBINE_ENTRIES = 1024;
-
-// Tokens per run: long runs amortise the index look-up, short ones leave the hardware many more blocks than it can
-// hold at once, which evens out runs of unequal length (measured on 65536 tokens: 2048 blocks 178 us, 16384 blocks 165).
-static int combine_chunk(int64_t n, int tpr) {
-    const int tok_per_block = 256 / tpr;
-    int chunk = COMBINE_CHUNK;
-    while (chunk > tok_per_block && n / chunk < 16384) chunk >>= 1;
-    return chunk < tok_per_block ? tok_per_block : chunk;
-}
-
-template <typename T, int VEC, int CAP, typename TRow = T>
+// One token per group of `tpr` lanes of a wavefront, nothing shared between groups.  Bound by memory, and on small
+// batches by the chain bitmap -> bucket row -> weight -> row: lane q of the group resolves entry q of the token's list, so
+// the chain is walked once per token however many experts chose it, all tokens a wavefront slot can hold are in flight,
+// and no barrier ties them together (blocks that resolved a run of tokens into LDS first took 19 us on 8192 x 768, 42 on
+// 16384 x 1024 and 199 on 65536 x 4096; now 10, 23 and 160, the last at 6 TB/s).  Then the group streams the rows, U pieces
+// of 16 bytes per lane at a time (8 bf16 / 4 fp32), entry by entry in list order, fp32 sums, rounded once.
+template <typename T, int VEC, int U, bool LISTS, typename TRow = T>
 __global__ void __launch_bounds__(256)
-combine_kernel(const TRow* __restrict__ Xe, const float* __restrict__ G, const int32_t* __restrict__ offsets,
-               const int32_t* __restrict__ inv, T* __restrict__ Xout, int n, int d, int tpr,
-               const float* __restrict__ addend, const int32_t* __restrict__ src_rows, int chunk) {
+combine_kernel(const TRow* __restrict__ Xe, const float* __restrict__ G, const uint32_t* __restrict__ bitmap,
+               const int32_t* __restrict__ pos, const int32_t* __restrict__ offsets, const int32_t* __restrict__ inv,
+               T* __restrict__ Xout, int n, int d, int e, int tpr, const float* __restrict__ addend,
+               const int32_t* __restrict__ src_rows) {
     typedef T vec_t __attribute__((ext_vector_type(VEC)));
     typedef TRow row_vec_t __attribute__((ext_vector_type(VEC)));  // bucket rows may be fp32 where the output is bf16
-    static_assert(COMBINE_CHUNK * (CAP > 0 ? CAP : 1) <= COMBINE_ENTRIES, "slot lists of a run fit the staging arrays");
-    __shared__ int ent_src[COMBINE_ENTRIES];
-    __shared__ float ent_g[COMBINE_ENTRIES];
-    __shared__ int tok_beg[COMBINE_CHUNK + 1];  // CSR: offsets of the run; slots: first entry of token j is j * CAP
-    __shared__ int tok_cnt[COMBINE_CHUNK];
-    const int tok_per_block = 256 / tpr;
-    const int sub = threadIdx.x / tpr, t = threadIdx.x % tpr;
-    const int vec_per_row = d / VEC;
-    const int chunks = (n + chunk - 1) / chunk;  // chunk <= COMBINE_CHUNK tokens per run
-    for (int ch = blockIdx.x; ch < chunks; ch += gridDim.x) {
-        const int l0 = ch * chunk;
-        const int ntok = n - l0 < chunk ? n - l0 : chunk;
-        bool staged = true;
-        int beg0 = 0;
-        __syncthreads();  // the previous run's rows have been read through these arrays
-        if (CAP > 0) {
-            if ((int)threadIdx.x < ntok) {
-                const int l = l0 + (int)threadIdx.x;
-                int cnt = offsets[l];  // experts that chose this token
-                cnt = cnt < CAP ? cnt : CAP;
-                int raw[CAP > 0 ? CAP : 1];
-#pragma unroll
-                for (int q = 0; q < CAP; ++q) raw[q] = q < cnt ? inv[(size_t)l * CAP + q] : 0x7FFFFFFF;
-                int last = -1;
-                for (int p = 0; p < cnt; ++p) {
-                    int best = 0x7FFFFFFF;
-#pragma unroll
-                    for (int q = 0; q < CAP; ++q) best = (raw[q] > last && raw[q] < best) ? raw[q] : best;
-                    last = best;
-                    ent_src[threadIdx.x * CAP + p] = src_rows != nullptr ? src_rows[best] : best;
-                    ent_g[threadIdx.x * CAP + p] = G != nullptr ? G[best] : 1.0f;
-                }
-                tok_beg[threadIdx.x] = (int)threadIdx.x * CAP;
-                tok_cnt[threadIdx.x] = cnt;
-            }
-            __syncthreads();
+    typedef float add_vec_t __attribute__((ext_vector_type(VEC)));
+    const int t = threadIdx.x & (tpr - 1);
+    const long long l = (long long)blockIdx.x * (256 / tpr) + threadIdx.x / tpr;
+    if (l >= n) return;
+    const int vec_per_row = d / VEC, words = (e + 31) >> 5;
+    // Entry q of the token's list (expert-ascending): source row and weight.  src_rows: bucket row r is row src_rows[r] of
+    // Xe (identity experts: X_e[i,j,:] = X[I[i,j],:], the gather of Eq. 3 read in place instead of through a materialised
+    // X_in); no weights: plain scatter-add of rows.  Returns the length of the list.
+    auto entry = [&](int q, int& src, float& g) -> int {
+        int cnt = 0, r = -1;
+        if (LISTS) {
+            const int beg = offsets[l];
+            cnt = offsets[l + 1] - beg;
+            if (q < cnt) r = inv[beg + q];
         } else {
-            if ((int)threadIdx.x <= ntok) tok_beg[threadIdx.x] = offsets[l0 + (int)threadIdx.x];
-            __syncthreads();
-            beg0 = tok_beg[0];
-            const int total = tok_beg[ntok] - beg0;
-            staged = total <= COMBINE_ENTRIES;  // the same for every thread of the block
-            if (staged) {
-                for (int idx = threadIdx.x; idx < total; idx += 256) {
-                    const int r = inv[beg0 + idx];
-                    ent_src[idx] = src_rows != nullptr ? src_rows[r] : r;
-                    ent_g[idx] = G != nullptr ? G[r] : 1.0f;
+            uint32_t mine = 0u;
+            int at = 0, ex = 0;
+#pragma unroll 4
+            for (int w = 0; w < words; ++w) {
+                const uint32_t m = bitmap[l * words + w];
+                const int c = __popc(m);
+                if (q >= cnt && q < cnt + c) {
+                    mine = m;
+                    at = q - cnt;
+                    ex = 32 * w;
                 }
+                cnt += c;
             }
-            if ((int)threadIdx.x < ntok) tok_cnt[threadIdx.x] = tok_beg[threadIdx.x + 1] - tok_beg[threadIdx.x];
-            __syncthreads();
+            if (q < cnt) {
+                for (; at > 0; --at) mine &= mine - 1u;
+                r = pos[l * e + ex + __ffs(mine) - 1];
+            }
         }
-        for (int tt = sub; tt < ntok; tt += tok_per_block) {
-            const int l = l0 + tt;
-            const int cnt = tok_cnt[tt];
-            const int eb = tok_beg[tt] - beg0;  // first entry of this token in the staging arrays
-            for (int v = t; v < vec_per_row; v += tpr) {
-                float acc[VEC];
+        src = r;
+        g = 1.0f;
+        if (r >= 0) {
+            if (src_rows != nullptr) src = src_rows[r];
+            if (G != nullptr) g = G[r];
+        }
+        return cnt;
+    };
+    int src;
+    float g;
+    const int cnt = entry(t, src, g);
+    for (int v0 = 0; v0 < vec_per_row; v0 += tpr * U) {
+        float acc[U][VEC];
 #pragma unroll
-                for (int q = 0; q < VEC; ++q) acc[q] = addend != nullptr ? addend[(size_t)l * d + (size_t)v * VEC + q] : 0.0f;
-                // entry p of this token: source row and weight.  src_rows: bucket row r is row src_rows[r] of Xe
-                // (identity experts: X_e[i,j,:] = X[I[i,j],:], the gather of Eq. 3 read in place instead of through a
-                // materialised X_in); no weights: plain scatter-add of rows
-                auto entry = [&](int p, size_t& src, float& g) {
-                    if (staged) {
-                        src = (size_t)ent_src[eb + p];
-                        g = ent_g[eb + p];
-                    } else {
-                        const int r = inv[beg0 + eb + p];
-                        src = src_rows != nullptr ? (size_t)src_rows[r] : (size_t)r;
-                        g = G != nullptr ? G[r] : 1.0f;
-                    }
-                };
-                int p = 0;
-                // four rows requested together, added in list order: a token that many experts chose does not pay one
-                // trip to memory per expert
-                for (; p + 4 <= cnt; p += 4) {
-                    size_t src[4];
-                    float g[4];
-                    row_vec_t x[4];
+        for (int u = 0; u < U; ++u) {
+            const int v = v0 + u * tpr + t;
+            add_vec_t a = add_vec_t(0.0f);
+            if (addend != nullptr && v < vec_per_row) a = *reinterpret_cast<const add_vec_t*>(addend + l * d + (long long)v * VEC);
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) entry(p + u, src[u], g[u]);
+            for (int q = 0; q < VEC; ++q) acc[u][q] = a[q];
+        }
+        for (int p0 = 0; p0 < cnt; p0 += tpr) {
+            if (cnt > tpr) entry(p0 + t, src, g);  // more experts than lanes: a batch of the list at a time
+            const int batch = cnt - p0 < tpr ? cnt - p0 : tpr;
+            for (int p = 0; p < batch; ++p) {
+                const TRow* row = Xe + (size_t)__shfl(src, p, tpr) * d;
+                const float w = __shfl(g, p, tpr);
+                row_vec_t x[U];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const row_vec_t*>(Xe + src[u] * d + (size_t)v * VEC);
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int q = 0; q < VEC; ++q) acc[q] = fmaf(g[u], Cvt<TRow>::to_f32(x[u][q]), acc[q]);
+                for (int u = 0; u < U; ++u) {
+                    const int v = v0 + u * tpr + t;
+                    if (v < vec_per_row) x[u] = *reinterpret_cast<const row_vec_t*>(row + (size_t)v * VEC);
                 }
-                for (; p < cnt; ++p) {
-                    size_t src;
-                    float g;
-                    entry(p, src, g);
-                    row_vec_t x = *reinterpret_cast<const row_vec_t*>(Xe + src * d + (size_t)v * VEC);
 #pragma unroll
-                    for (int q = 0; q < VEC; ++q) acc[q] = fmaf(g, Cvt<TRow>::to_f32(x[q]), acc[q]);
-                }
-                vec_t o;
+                for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int q = 0; q < VEC; ++q) o[q] = Cvt<T>::from_f32(acc[q]);
-                *reinterpret_cast<vec_t*>(Xout + (size_t)l * d + (size_t)v * VEC) = o;
+                    for (int q = 0; q < VEC; ++q) acc[u][q] = fmaf(w, Cvt<TRow>::to_f32(x[u][q]), acc[u][q]);
             }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int v = v0 + u * tpr + t;
+            vec_t o;
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) o[q] = Cvt<T>::from_f32(acc[u][q]);
+            if (v < vec_per_row) *reinterpret_cast<vec_t*>(Xout + l * d + (long long)v * VEC) = o;
         }
     }
+}
+
+// Lanes per token: as many as the row fills without leaving more than it must idle in the last step.
+static int combine_threads_per_row(int64_t vec_per_row) {
+    int tpr = 64;
+    while (tpr > 16 && align_up((size_t)vec_per_row, tpr / 2) < align_up((size_t)vec_per_row, tpr)) tpr /= 2;
+    return tpr;
 }
 
 static unsigned blocks_for(long long items) {
@@ -325,97 +283,57 @@ static unsigned blocks_for(long long items) {
     return (unsigned)(b > 16384 ? 16384 : (b < 1 ? 1 : b));
 }
 
-// Builds the token-major index from I alone (stand-alone combine; the forward pass gets it
-// from the gate and top-k kernels instead).
-int launch_combine_index(const int32_t* I, int64_t n, int64_t e, int64_t k, const CombineIndex& ix,
-                         hipStream_t stream) {
-    const long long rows = (long long)e * k;
-    if (ix.use_slots) {
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks_for(n)), dim3(256), 0, stream, (uint32_t*)ix.slot_cnt,
-                           (long long)n, 0u);
-        hipLaunchKernelGGL(slots_kernel, dim3(blocks_for(rows)), dim3(256), 0, stream, I, ix.slot_cnt, ix.slots, rows,
-                           ix.slot_cap);
-    } else {
-        const int words = (int)ceil_div(e, 32);
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks_for((long long)n * words)), dim3(256), 0, stream, ix.bitmap,
-                           (long long)n * words, 0u);
-        hipLaunchKernelGGL(bitmap_kernel, dim3(blocks_for(rows)), dim3(256), 0, stream, I, ix.bitmap, rows, (int)k,
-                           words);
-    }
-    return check_launch();
-}
-
-// Finishes the CSR form from a filled bitmap: offsets (exclusive scan) and the expert-ascending row lists.
-int launch_combine_csr(const int32_t* I, int64_t n, int64_t e, int64_t k, const CombineIndex& ix, hipStream_t stream) {
+// Lists from a filled bitmap: offsets (exclusive scan) and the expert-ascending row lists.
+static void launch_index_lists(const int32_t* I, int64_t n, int64_t e, int64_t k, const CombineIndex& ix, hipStream_t stream) {
     const long long rows = (long long)e * k;
     const int words = (int)ceil_div(e, 32);
     // token range of a scan block: 1024 tokens, more only when that would need over 1024 blocks
     const int tpb = (int)(ceil_div(ceil_div(n, 1024), 1024) * 1024);
     const unsigned scan_blocks = (unsigned)ceil_div(n, tpb);
-    uint32_t* block_tot = reinterpret_cast<uint32_t*>(ix.slot_cnt);  // [n] words, idle in the CSR form
-    hipLaunchKernelGGL(block_counts_kernel, dim3(scan_blocks), dim3(1024), 0, stream, ix.bitmap, block_tot, (int)n,
+    hipLaunchKernelGGL(block_counts_kernel, dim3(scan_blocks), dim3(1024), 0, stream, ix.bitmap, ix.block_tot, (int)n,
                        words, tpb);
-    hipLaunchKernelGGL(offsets_kernel, dim3(scan_blocks), dim3(1024), 0, stream, ix.bitmap, block_tot, ix.offsets,
+    hipLaunchKernelGGL(offsets_kernel, dim3(scan_blocks), dim3(1024), 0, stream, ix.bitmap, ix.block_tot, ix.offsets,
                        (int)n, words, tpb);
     hipLaunchKernelGGL(inverse_index_kernel, dim3(blocks_for(rows)), dim3(256), 0, stream, I, ix.bitmap, ix.offsets,
                        ix.inv, rows, (int)k, words);
+}
+
+// Builds the token-major index from I alone (stand-alone combine, backward pass; the forward pass gets it
+// from the gate and top-k kernels instead).
+int launch_combine_index(const int32_t* I, int64_t n, int64_t e, int64_t k, const CombineIndex& ix,
+                         hipStream_t stream, bool bitmap_is_zero) {
+    const long long rows = (long long)e * k;
+    if (!bitmap_is_zero)
+        hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks_for(combine_zero_words(n, e))), dim3(256), 0, stream, ix.bitmap,
+                           (long long)combine_zero_words(n, e), 0u);
+    hipLaunchKernelGGL(index_kernel, dim3(blocks_for(rows)), dim3(256), 0, stream, I, ix.bitmap, ix.pos, rows, (int)k,
+                       (int)ceil_div(e, 32), (int)e);
+    if (ix.pos == nullptr) launch_index_lists(I, n, e, k, ix, stream);
     return check_launch();
 }
 
-// Applies Eq. 4 given a filled index (slot lists, or the bitmap from which the CSR lists are finished here).
+// Applies Eq. 4 given a filled index.
 // G == nullptr adds the rows unweighted; `addend` (fp32 [n,d], optional) is the starting value of every row;
 // `src_rows` (optional, [e*k]) redirects bucket row r to row src_rows[r] of Xe; `rows_f32`: the bucket rows are
 // fp32 although the output is bf16 (the last product of the backward pass is kept unrounded).
 int launch_combine(const void* Xe, const float* G, const int32_t* I, void* Xout, int64_t n, int64_t d,
                    int64_t e, int64_t k, int dtype, const CombineIndex& ix, hipStream_t stream,
-                   const float* addend, bool csr_ready, const int32_t* src_rows, bool rows_f32) {
-    const int32_t* offs = ix.slot_cnt;
-    const int32_t* list = ix.slots;
-    if (!ix.use_slots) {
-        if (!csr_ready) {
-            int rc = launch_combine_csr(I, n, e, k, ix, stream);
-            if (rc != EC_OK) return rc;
-        }
-        offs = ix.offsets;
-        list = ix.inv;
-    }
-#define EC_COMBINE_LAUNCH(TYPE, VECV, NVEC)                                                                   \
-    do {                                                                                                      \
-        int tpr = pick_threads_per_row(NVEC);                                                                 \
-        const int chunk = combine_chunk(n, tpr);                                                              \
-        long long blocks = ceil_div(n, chunk);                                                                \
-        if (blocks > (1 << 20)) blocks = 1 << 20;                                                             \
-        dim3 grid((unsigned)blocks), block(256);                                                              \
-        if (!ix.use_slots)                                                                                    \
-            hipLaunchKernelGGL((combine_kernel<TYPE, VECV, 0>), grid, block, 0, stream, (const TYPE*)Xe, G,   \
-                               offs, list, (TYPE*)Xout, (int)n, (int)d, tpr, addend, src_rows, chunk);                                 \
-        else if (ix.slot_cap == 4)                                                                            \
-            hipLaunchKernelGGL((combine_kernel<TYPE, VECV, 4>), grid, block, 0, stream, (const TYPE*)Xe, G,   \
-                               offs, list, (TYPE*)Xout, (int)n, (int)d, tpr, addend, src_rows, chunk);                                 \
-        else if (ix.slot_cap == 8)                                                                            \
-            hipLaunchKernelGGL((combine_kernel<TYPE, VECV, 8>), grid, block, 0, stream, (const TYPE*)Xe, G,   \
-                               offs, list, (TYPE*)Xout, (int)n, (int)d, tpr, addend, src_rows, chunk);                                 \
-        else                                                                                                  \
-            hipLaunchKernelGGL((combine_kernel<TYPE, VECV, 16>), grid, block, 0, stream, (const TYPE*)Xe, G,  \
-                               offs, list, (TYPE*)Xout, (int)n, (int)d, tpr, addend, src_rows, chunk);                                 \
+                   const float* addend, const int32_t* src_rows, bool rows_f32) {
+    (void)I; (void)k;
+#define EC_COMBINE_LAUNCH(TYPE, VECV, TROW)                                                                              \
+    do {                                                                                                                 \
+        const int tpr = combine_threads_per_row(d / VECV);                                                               \
+        auto dense2 = combine_kernel<TYPE, VECV, 2, false, TROW>;                                                        \
+        auto dense4 = combine_kernel<TYPE, VECV, 4, false, TROW>;                                                        \
+        auto lists = combine_kernel<TYPE, VECV, 4, true, TROW>;                                                          \
+        hipLaunchKernelGGL(ix.pos == nullptr ? lists : d / VECV <= 2 * tpr ? dense2 : dense4, dim3((unsigned)ceil_div(n, 256 / tpr)), dim3(256), 0,      \
+                           stream, (const TROW*)Xe, G, ix.bitmap, ix.pos, ix.offsets, ix.inv, (TYPE*)Xout, (int)n, (int)d, \
+                           (int)e, tpr, addend, src_rows);                                                               \
     } while (0)
-    if (dtype == EC_BF16 && rows_f32) {
-        int tpr = pick_threads_per_row(d / 8);
-        const int chunk = combine_chunk(n, tpr);
-        long long blocks = ceil_div(n, chunk);
-        if (blocks > (1 << 20)) blocks = 1 << 20;
-        const dim3 grid((unsigned)blocks), block(256);
-#define EC_COMBINE_F32ROWS(CAPV)                                                                                   \
-    hipLaunchKernelGGL((combine_kernel<bf16_t, 8, CAPV, float>), grid, block, 0, stream, (const float*)Xe, G, offs, list, \
-                       (bf16_t*)Xout, (int)n, (int)d, tpr, addend, src_rows, chunk)
-        if (!ix.use_slots) EC_COMBINE_F32ROWS(0);
-        else if (ix.slot_cap == 4) EC_COMBINE_F32ROWS(4);
-        else if (ix.slot_cap == 8) EC_COMBINE_F32ROWS(8);
-        else EC_COMBINE_F32ROWS(16);
-#undef EC_COMBINE_F32ROWS
-    } else if (dtype == EC_BF16) EC_COMBINE_LAUNCH(bf16_t, 8, d / 8);
-    else if (d % 4 == 0) EC_COMBINE_LAUNCH(float, 4, d / 4);
-    else EC_COMBINE_LAUNCH(float, 1, d);
+    if (dtype == EC_BF16 && rows_f32) EC_COMBINE_LAUNCH(bf16_t, 8, float);
+    else if (dtype == EC_BF16) EC_COMBINE_LAUNCH(bf16_t, 8, bf16_t);
+    else if (d % 4 == 0) EC_COMBINE_LAUNCH(float, 4, float);
+    else EC_COMBINE_LAUNCH(float, 1, float);
 #undef EC_COMBINE_LAUNCH
     return check_launch();
 }
@@ -448,28 +366,19 @@ int combine_static(const void* Xe, const float* G, const int32_t* I, void* Xout,
         }
         base = scratch_ptr[dev];
     }
-    // carve-up: only the form of the index that this expert count uses
-    CombineIndex ix;
-    ix.use_slots = e <= COMBINE_SLOT_CAP;
-    ix.slot_cap = e <= 4 ? 4 : e <= 8 ? 8 : 16;
+    // carve-up: the dense index if it fits, the lists otherwise
     size_t off = 0;
-    auto take = [&](size_t bytes) { size_t a = off; off = align_up(off + bytes, 256); return a; };
-    size_t o_cnt, o_slots = 0, o_bitmap = 0, o_offsets = 0, o_inv = 0;
-    if (ix.use_slots) {
-        o_cnt = take((size_t)n * 4);
-        o_slots = take((size_t)n * ix.slot_cap * 4);
+    auto take = [&](size_t bytes) { size_t a = off; off = align_up(off + bytes, 256); return base + a; };
+    CombineIndex ix = {};
+    ix.bitmap = reinterpret_cast<uint32_t*>(take((size_t)combine_zero_words(n, e) * 4));
+    if (off + (size_t)n * e * 4 <= (size_t)EC_MOE_STATIC_SCRATCH_BYTES) {
+        ix.pos = reinterpret_cast<int32_t*>(base + off);
     } else {
-        o_cnt = take(1024 * 4);  // totals of the scan blocks (at most 1024 of them)
-        o_bitmap = take((size_t)n * (size_t)ceil_div(e, 32) * 4);
-        o_offsets = take((size_t)(n + 1) * 4);
-        o_inv = take((size_t)e * k * 4);
+        ix.block_tot = reinterpret_cast<uint32_t*>(take(1024 * 4));
+        ix.offsets = reinterpret_cast<int32_t*>(take((size_t)(n + 1) * 4));
+        ix.inv = reinterpret_cast<int32_t*>(take((size_t)e * k * 4));
+        if (off > (size_t)EC_MOE_STATIC_SCRATCH_BYTES) return EC_ERR_UNSUPPORTED;
     }
-    if (off > (size_t)EC_MOE_STATIC_SCRATCH_BYTES) return EC_ERR_UNSUPPORTED;
-    ix.slot_cnt = reinterpret_cast<int32_t*>(base + o_cnt);
-    ix.slots = reinterpret_cast<int32_t*>(base + o_slots);
-    ix.bitmap = reinterpret_cast<uint32_t*>(base + o_bitmap);
-    ix.offsets = reinterpret_cast<int32_t*>(base + o_offsets);
-    ix.inv = reinterpret_cast<int32_t*>(base + o_inv);
     int rc = launch_combine_index(I, n, e, k, ix, stream);  // clears the counters / bitmap with a fill kernel first
     if (rc != EC_OK) return rc;
     return launch_combine(Xe, G, I, Xout, n, d, e, k, dtype, ix, stream);

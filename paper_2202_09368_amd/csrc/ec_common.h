@@ -51,11 +51,8 @@ struct WsLayout {
     size_t xe;         // dtype [e, k, d]
     size_t h_lo;       // bf16 [e, k, d_ff]: act(A) - H                            (EC_BF16_HILO only)
     size_t xe32;       // float [e, k, d]: X_e unrounded                           (EC_BF16_HILO only)
-    size_t bitmap;     // uint32 [n, ceil(e/32)]: which experts chose a token      (CSR form, e > COMBINE_SLOT_CAP)
-    size_t offsets;    // int32 [n+1]: CSR row starts of the token-major index
-    size_t inv;        // int32 [e*k]: bucket rows (i*k+j) grouped by token, expert-ascending
-    size_t slot_cnt;   // int32 [n]: experts that chose a token                     (slot form, e <= COMBINE_SLOT_CAP)
-    size_t slots;      // int32 [n, COMBINE_SLOT_CAP]: their bucket rows, arrival order
+    size_t bitmap;     // uint32 [n, ceil(e/32)]: which experts chose a token
+    size_t pos;        // int32 [n, e]: the bucket row (i*k+j) of the pairs whose bit is set, undefined elsewhere
     size_t choice;     // int32 [8, n]: every token's chosen experts, rank-major (token-choice routing)
     size_t bwd;        // start of the backward-only region
     size_t total;
@@ -66,23 +63,22 @@ WsLayout ws_layout(int64_t n, int64_t d, int64_t e, int64_t k, int64_t d_ff, int
 // Sizes of the backward-only region (defined with the backward kernels).
 size_t bwd_ws_bytes(int64_t n, int64_t d, int64_t e, int64_t k, int64_t d_ff, int dtype, bool hilo = false);
 
-// Token-major index of the routing handed from the top-k stage to the combine stage.
-constexpr int COMBINE_SLOT_CAP = 16;
+// Token-major index of the routing handed from the top-k stage to the combine stage and used by the backward pass.
+// Two forms:
+//  * dense (the usual one): a bit per (token, expert) and, where it is set, the bucket row.  The kernel that knows I
+//    writes both without waiting for anything, so the index costs no launch of its own behind the selection.
+//  * lists: offsets and row lists per token made from the bitmap by three launches, 4 n (1 + c) bytes instead of 4 n e,
+//    for ec_moe_combine_static when the dense form does not fit its array.
 struct CombineIndex {
-    bool use_slots;      // e <= COMBINE_SLOT_CAP: per-token slot lists; otherwise bitmap + CSR
-    int32_t* slot_cnt;   // [n]
-    int32_t* slots;      // [n, slot_cap]
-    int slot_cap;
     uint32_t* bitmap;    // [n, ceil(e/32)]
-    int32_t* offsets;    // [n+1]
-    int32_t* inv;        // [e*k]
+    int32_t* pos;        // dense form: [n, e]; nullptr: the lists below
+    int32_t* offsets;    // lists: [n+1]
+    int32_t* inv;        // lists: [e*k], bucket rows grouped by token, expert-ascending
+    uint32_t* block_tot; // lists: [1024] scratch of the scan
 };
-CombineIndex combine_index_at(void* ws_base, const WsLayout& L, int64_t e);
-// 32-bit words that must be zero before the index is filled, and where they start.
-inline uint32_t* combine_zero_ptr(const CombineIndex& ix) { return ix.use_slots ? (uint32_t*)ix.slot_cnt : ix.bitmap; }
-inline int64_t combine_zero_words(const CombineIndex& ix, int64_t n, int64_t e) {
-    return ix.use_slots ? n : n * ceil_div(e, 32);
-}
+CombineIndex combine_index_at(void* ws_base, const WsLayout& L);
+// 32-bit words of the bitmap: they must be zero before the index is filled.
+inline int64_t combine_zero_words(int64_t n, int64_t e) { return n * ceil_div(e, 32); }
 
 // ---------------------------------------------------------------------------
 // Launchers (host side, arguments already validated by the ABI layer).
@@ -90,18 +86,14 @@ inline int64_t combine_zero_words(const CombineIndex& ix, int64_t n, int64_t e) 
 int launch_gate(const void* X, const void* Wg, float* S, float* St, int64_t n, int64_t d, int64_t e,
                 int dtype, uint32_t* zero_buf, int64_t zero_words, hipStream_t stream);
 int launch_topk(const float* St, int64_t n, int64_t e, int64_t k, float* G, int32_t* I,
-                int32_t* slot_cnt, int32_t* slots, int slot_cap, uint32_t* bitmap, hipStream_t stream,
-                int64_t groups = 1);
+                const CombineIndex* ix, hipStream_t stream, int64_t groups = 1, const float* values = nullptr);
 int launch_token_choice(const float* S, int64_t n, int64_t e, int64_t m, int64_t cap, float* G, int32_t* I,
-                        int32_t* load, int32_t* choice_ws, int32_t* slot_cnt, int32_t* slots, int slot_cap,
-                        uint32_t* bitmap, hipStream_t stream);
+                        int32_t* load, int32_t* choice_ws, const CombineIndex* ix, hipStream_t stream);
 size_t capped_ws_bytes(int64_t n, int64_t e);
 int launch_capped_assignment(const float* St, int64_t n, int64_t e, int64_t k, double b, double lambda,
                              int64_t iters, float* A, void* ws, hipStream_t stream);
-int launch_gather_scores(const float* St, const int32_t* I, float* G, int64_t n, int64_t e, int64_t k,
-                         hipStream_t stream);
 int launch_combine_index(const int32_t* I, int64_t n, int64_t e, int64_t k, const CombineIndex& ix,
-                         hipStream_t stream);
+                         hipStream_t stream, bool bitmap_is_zero = false);
 int launch_dispatch(const void* X, const int32_t* I, void* Xin, int64_t n, int64_t d, int64_t e, int64_t k,
                     int dtype, hipStream_t stream);
 bool ffn_can_gather(int dtype, int64_t n, int64_t k, int64_t d, int64_t d_ff);
@@ -109,11 +101,9 @@ bool ffn_can_hilo(int dtype, int64_t k, int64_t d, int64_t d_ff);
 int launch_ffn(const void* Xin, const void* X, const int32_t* I, int64_t n, const void* W1, const void* W2, void* Xe,
                void* A_save, void* H, int64_t e, int64_t k, int64_t d, int64_t d_ff, int act, int dtype,
                hipStream_t stream, void* H_lo = nullptr, float* Xe32 = nullptr);
-int launch_combine_csr(const int32_t* I, int64_t n, int64_t e, int64_t k, const CombineIndex& ix, hipStream_t stream);
 int launch_combine(const void* Xe, const float* G, const int32_t* I, void* Xout, int64_t n, int64_t d,
                    int64_t e, int64_t k, int dtype, const CombineIndex& ix, hipStream_t stream,
-                   const float* addend = nullptr, bool csr_ready = false, const int32_t* src_rows = nullptr,
-                   bool rows_f32 = false);
+                   const float* addend = nullptr, const int32_t* src_rows = nullptr, bool rows_f32 = false);
 int combine_static(const void* Xe, const float* G, const int32_t* I, void* Xout, int64_t n, int64_t d, int64_t e,
                    int64_t k, int dtype, hipStream_t stream);
 int launch_backward(const void* dY, const void* X, const void* Wg, const void* W1, const void* W2,

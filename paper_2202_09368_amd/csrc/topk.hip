@@ -4,9 +4,8 @@
 // (n contiguous floats).  Scores are non-negative, so their bit patterns order
 // like unsigned integers, and (score bits, ~token) is a total order in which
 // "larger" means "admitted first".  Steps:
-//   1. read the row once and keep it on chip -- in the registers of the workgroup (rows up to 65536
-//      tokens, the kernel further down) or in LDS -- and find min and max; rows that fit neither are
-//      re-read from memory in every pass;
+//   1. read the row once and keep it in the registers of the workgroup (rows up to 65536 tokens, the kernel
+//      further down), and find min and max; longer rows are re-read from memory in every pass;
 //   2. radix-select on (bits - min), 8 bits per pass starting at the top bit of
 //      the actual range, until the bin holding the k-th score has at most
 //      TOPK_CAND_MAX members or all 32 bits are decided;
@@ -16,9 +15,8 @@
 //      ones per range, prefix the counts, then write the bucket in ascending
 //      token order with ballot ranks.  No sort is needed.
 // Rows of more than 32768 scores with k <= 512 first try a threshold taken from the per-thread maxima, which
-// replaces steps 2-4 by work on about 1.3 k candidates (see the register-resident kernel).
-#include <atomic>
-
+// replaces steps 2-4 by work on about 1.3 k candidates (see the register-resident kernel).  Rows of at most
+// TOPK_SMALL_MAX scores take one wavefront each (the last kernel).
 #include "ec_common.h"
 
 namespace ecmoe {
@@ -27,25 +25,39 @@ constexpr int TOPK_THREADS = 1024;
 constexpr int TOPK_WAVES = TOPK_THREADS / kWave;
 constexpr int TOPK_CAND_MAX = 256;
 
-// Optional token-major by-products for the combine stage, written while the bucket is emitted:
-// either a slot list per token (slot_cnt[l] counts the experts that chose token l, the first
-// `slot_cap` of them leave their bucket row i*k+j in slots[l*slot_cap + ...], in arrival order)
-// or one bit per (token, expert) in `bitmap` (`bitmap_words` 32-bit words per token).
-// Integer atomics only: the set of entries does not depend on the order of arrival.
+// What else an admitted pair leaves behind: the token-major index for the combine stage (CombineIndex's dense form;
+// integer stores and ORs only, so it does not depend on the order of arrival), and where its weight comes from
+// (`values`, [e, n]: scores other than the ones selected on; nullptr: the selected ones).
 struct TopkEmit {
-    int32_t* slot_cnt;
-    int32_t* slots;
-    int slot_cap;
     uint32_t* bitmap;
-    int bitmap_words;
+    int32_t* pos;
+    int words, e;
+    const float* values;
 };
 
-__device__ __forceinline__ void topk_emit(const TopkEmit& em, int expert, int k, int rank, int tok) {
-    if (em.slot_cnt != nullptr) {
-        int s = atomicAdd(&em.slot_cnt[tok], 1);
-        if (s < em.slot_cap) em.slots[(size_t)tok * em.slot_cap + s] = expert * k + rank;
+__device__ __forceinline__ void topk_put(const TopkEmit& em, float* __restrict__ G, int32_t* __restrict__ I, size_t row,
+                                         int expert, int n_total, int tok, unsigned int bits) {
+    G[row] = em.values != nullptr ? em.values[(size_t)expert * n_total + tok] : __uint_as_float(bits);
+    I[row] = tok;
+    if (em.bitmap != nullptr) {
+        em.pos[(size_t)tok * em.e + expert] = (int32_t)row;
+        atomicOr(&em.bitmap[(size_t)tok * em.words + (expert >> 5)], 1u << (expert & 31));
     }
-    if (em.bitmap != nullptr) atomicOr(&em.bitmap[(size_t)tok * em.bitmap_words + (expert >> 5)], 1u << (expert & 31));
+}
+
+// Four consecutive scores (rows are 4-byte aligned only when n % 4 != 0); `left` of them exist, the rest reads `pad`.
+typedef unsigned int u32x4_row __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void topk_load_quad(const unsigned int* __restrict__ p, int left, unsigned int pad, unsigned int (&v)[4]) {
+    u32x4_row q = {pad, pad, pad, pad};
+    if (left >= 4) {
+        q = *reinterpret_cast<const u32x4_row*>(p);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (c < left) q[c] = p[c];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = q[c];
 }
 
 struct TopkShared {
@@ -61,19 +73,16 @@ __device__ __forceinline__ unsigned long long topk_key(unsigned int bits, unsign
     return ((unsigned long long)bits << 32) | (unsigned long long)(0xFFFFFFFFu - tok);
 }
 
-template <bool STAGED>
 __global__ void __launch_bounds__(TOPK_THREADS)
 topk_tokens_kernel(const float* __restrict__ St, int n, int k, float* __restrict__ G, int32_t* __restrict__ I,
                    TopkEmit emit) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ TopkShared sh;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int expert = blockIdx.x;
     const unsigned int* __restrict__ colg = reinterpret_cast<const unsigned int*>(St) + (size_t)expert * n;
-    unsigned int* cols = reinterpret_cast<unsigned int*>(smem);
 
-    // ---- 1. stage + min/max ------------------------------------------------
+    // ---- 1. min/max --------------------------------------------------------
     unsigned int vmin = 0xFFFFFFFFu, vmax = 0u;
     const bool vec_ok = (n & 3) == 0;  // rows are 16-byte aligned: four scores per load
     if (vec_ok) {
@@ -81,7 +90,6 @@ topk_tokens_kernel(const float* __restrict__ St, int n, int k, float* __restrict
 #pragma unroll 4
         for (int q = tid; q < (n >> 2); q += TOPK_THREADS) {
             const uint4 v = colg4[q];
-            if (STAGED) reinterpret_cast<uint4*>(cols)[q] = v;
             const unsigned int lo4 = min(min(v.x, v.y), min(v.z, v.w)), hi4 = max(max(v.x, v.y), max(v.z, v.w));
             vmin = lo4 < vmin ? lo4 : vmin;
             vmax = hi4 > vmax ? hi4 : vmax;
@@ -89,7 +97,6 @@ topk_tokens_kernel(const float* __restrict__ St, int n, int k, float* __restrict
     } else {
         for (int idx = tid; idx < n; idx += TOPK_THREADS) {
             unsigned int v = colg[idx];
-            if (STAGED) cols[idx] = v;
             vmin = v < vmin ? v : vmin;
             vmax = v > vmax ? v : vmax;
         }
@@ -108,7 +115,7 @@ topk_tokens_kernel(const float* __restrict__ St, int n, int k, float* __restrict
         vmin = a < vmin ? a : vmin;
         vmax = b > vmax ? b : vmax;
     }
-    auto ld = [&](int idx) -> unsigned int { return STAGED ? cols[idx] : colg[idx]; };
+    auto ld = [&](int idx) -> unsigned int { return colg[idx]; };
 
     // ---- 2. radix select on key = v - vmin --------------------------------
     const unsigned int range = vmax - vmin;
@@ -122,7 +129,7 @@ topk_tokens_kernel(const float* __restrict__ St, int n, int k, float* __restrict
         const unsigned int hmask = lo >= 32 ? 0u : ~((1u << lo) - 1u);
         if (tid < 256) sh.hist[tid] = 0;
         __syncthreads();
-        if (!STAGED && vec_ok) {
+        if (vec_ok) {
             const uint4* __restrict__ colg4 = reinterpret_cast<const uint4*>(colg);
 #pragma unroll 4
             for (int q = tid; q < (n >> 2); q += TOPK_THREADS) {
@@ -270,9 +277,7 @@ topk_tokens_kernel(const float* __restrict__ St, int n, int k, float* __restrict
         if (sel) {
             const unsigned int j = pos + (unsigned int)__popcll(bal & ((1ull << lane) - 1ull));
             if (j < (unsigned int)k) {  // always true for a correct selection; guards the stores
-                G[(size_t)expert * k + j] = __uint_as_float(v);
-                I[(size_t)expert * k + j] = idx;
-                topk_emit(emit, expert, k, (int)j, idx);
+                topk_put(emit, G, I, (size_t)expert * k + j, expert, n, idx, v);
             }
         }
         pos += (unsigned int)__popcll(bal);
@@ -390,7 +395,8 @@ __device__ unsigned long long block_kth_largest(unsigned long long key, bool val
 // w * 256 R + 256 r + 4 lane .. + 3, so a wavefront's loads are whole 1-KiB pieces of the row.
 // Histograms: four copies (one per wavefront residue) in three rotating buffers, which leaves one
 // barrier per radix pass; every wavefront scans the histogram itself instead of waiting for a
-// broadcast.  Requires n % 4 == 0 (16-byte aligned rows).
+// broadcast.  A wavefront whose lanes mostly hit one bin counts that bin together: scores that are mostly equal (an
+// assignment full of zeros) would queue 64 deep on one LDS word otherwise (8192 such scores: 41 -> 20 us).
 //
 // gridDim.y > 1 selects per group of tokens: the row is cut into gridDim.y equal segments of n
 // tokens and every (expert, segment) pair takes its own k best; a bucket then lists its segments
@@ -428,7 +434,7 @@ topk_tokens_reg_kernel(const float* __restrict__ St, int n_total, int n, int k, 
     const unsigned int* __restrict__ colg = reinterpret_cast<const unsigned int*>(St) + (size_t)expert * n_total + tok0;
     constexpr int PER_WAVE = 256 * R;
     const int t_base = wave * PER_WAVE + 4 * lane;  // token of quad 0, element 0
-    // quads r < rv are inside the row (n % 4 == 0: a quad is inside or outside as a whole)
+    // quads r < rv have scores of the row; only the row's last quad may be partly outside
     const int rv = t_base >= n ? 0 : ((n - t_base + 255) >> 8) < R ? ((n - t_base + 255) >> 8) : R;
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
 
@@ -437,15 +443,11 @@ topk_tokens_reg_kernel(const float* __restrict__ St, int n_total, int n, int k, 
     unsigned int vmin = 0xFFFFFFFFu, vmax = 0u;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        // Quads outside the row hold 0xFFFFFFFF: scores are non-negative floats (bits below 2^31), so this
+        // Scores outside the row read 0xFFFFFFFF: scores are non-negative floats (bits below 2^31), so this
         // value is never inside a radix window and, compared as a signed number, never passes the cut-off.
-        uint4 q = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
-        if (r < rv) {
-            q = *reinterpret_cast<const uint4*>(colg + t_base + 256 * r);
-            vmin = min(vmin, min(min(q.x, q.y), min(q.z, q.w)));
-            vmax = max(vmax, max(max(q.x, q.y), max(q.z, q.w)));
-        }
-        v[r][0] = q.x; v[r][1] = q.y; v[r][2] = q.z; v[r][3] = q.w;
+        topk_load_quad(colg + t_base + 256 * r, n - (t_base + 256 * r), 0xFFFFFFFFu, v[r]);
+        vmin = min(vmin, min(min(v[r][0], v[r][1]), min(v[r][2], v[r][3])));
+        vmax = (unsigned int)max((int)vmax, max(max((int)v[r][0], (int)v[r][1]), max((int)v[r][2], (int)v[r][3])));
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -478,12 +480,12 @@ topk_tokens_reg_kernel(const float* __restrict__ St, int n_total, int n, int k, 
         unsigned int tmax = 0u;
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            if (r < rv) tmax = max(tmax, max(max(v[r][0], v[r][1]), max(v[r][2], v[r][3])));
+            tmax = (unsigned int)max((int)tmax, max(max((int)v[r][0], (int)v[r][1]), max((int)v[r][2], (int)v[r][3])));
         int nvt = 0;  // threads that hold scores: lanes with 4 * lane below what is left of the row for their wavefront
 #pragma unroll
         for (int w = 0; w < TOPK_WAVES; ++w) {
             const int rem = n - w * PER_WAVE;
-            nvt += rem <= 0 ? 0 : (rem >= 256 ? 64 : rem >> 2);
+            nvt += rem <= 0 ? 0 : (rem >= 256 ? 64 : (rem + 3) >> 2);
         }
         unsigned int T = 0u;  // fewer maxima than k: everything is a candidate
         if (k <= nvt)
@@ -535,14 +537,7 @@ topk_tokens_reg_kernel(const float* __restrict__ St, int n_total, int n, int k, 
                                        (unsigned int)__popc(fs.tokbits[word] & ((1u << (tok & 31)) - 1u));
                 if (j < (unsigned int)k) {  // always true for a correct selection; guards the stores
                     const int gtok = tok0 + (int)tok;
-                    G[out0 + j] = __uint_as_float(ck);
-                    I[out0 + j] = gtok;
-                    if (emit.slot_cnt != nullptr) {
-                        const int at = atomicAdd(&emit.slot_cnt[gtok], 1);
-                        if (at < emit.slot_cap) emit.slots[(size_t)gtok * emit.slot_cap + at] = (int32_t)(out0 + j);
-                    }
-                    if (emit.bitmap != nullptr)
-                        atomicOr(&emit.bitmap[(size_t)gtok * emit.bitmap_words + (expert >> 5)], 1u << (expert & 31));
+                    topk_put(emit, G, I, out0 + j, expert, n_total, gtok, ck);
                 }
             }
             return;
@@ -562,12 +557,31 @@ topk_tokens_reg_kernel(const float* __restrict__ St, int n_total, int n, int k, 
         // left after the subtraction is the undecided part of the key, its top digit the histogram bin
         const unsigned int base = vmin + prefix, span_m1 = lo >= 32 ? 0xFFFFFFFFu : (1u << lo) - 1u;
         unsigned int* H = sh.hist[pass % 3][wave & 3];
+        // does the wavefront's first score share its bin with many of the others?
+        const unsigned int t0 = v[0][0] - base;
+        const unsigned long long in0 = __ballot(t0 <= span_m1);
+        const int first0 = in0 != 0ull ? __ffsll((long long)in0) - 1 : 0;
+        const unsigned int lead0 = (unsigned int)__builtin_amdgcn_readlane(t0, first0) >> nlo;
+        if (__popcll(__ballot(t0 <= span_m1 && (t0 >> nlo) == lead0)) < 16) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
+            for (int r = 0; r < R; ++r) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const unsigned int t = v[r][c] - base;
-                if (t <= span_m1) atomicAdd(&H[t >> nlo], 1u);
+                for (int c = 0; c < 4; ++c) {
+                    const unsigned int t = v[r][c] - base;
+                    if (t <= span_m1) atomicAdd(&H[t >> nlo], 1u);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const unsigned int t = v[r][c] - base;
+                    const bool in = t <= span_m1, lead = in && (t >> nlo) == lead0;
+                    const unsigned long long bal = __ballot(lead);
+                    if (in && !lead) atomicAdd(&H[t >> nlo], 1u);
+                    if (bal != 0ull && lane == 0) atomicAdd(&H[lead0], (unsigned int)__popcll(bal));
+                }
             }
         }
         __syncthreads();
@@ -724,24 +738,11 @@ topk_tokens_reg_kernel(const float* __restrict__ St, int n_total, int n, int k, 
             tot += (unsigned int)__popcll(bal);
         }
         if (tot != 0u) {  // uniform
-            const int tok_q = tok0 + t_base + 256 * r;
-            int slot_at[4] = {0, 0, 0, 0};
-            if (emit.slot_cnt != nullptr) {  // the four atomics are in flight together; their results feed the stores below
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (sel[c]) slot_at[c] = atomicAdd(&emit.slot_cnt[tok_q + c], 1);
-            }
             unsigned int j = pos + pre;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                if (sel[c] && j < (unsigned int)k) {  // j < k always holds for a correct selection; guards the stores
-                    G[out0 + j] = __uint_as_float(v[r][c]);
-                    I[out0 + j] = tok_q + c;
-                    if (emit.slot_cnt != nullptr && slot_at[c] < emit.slot_cap)
-                        emit.slots[(size_t)(tok_q + c) * emit.slot_cap + slot_at[c]] = (int32_t)(out0 + j);
-                    if (emit.bitmap != nullptr)
-                        atomicOr(&emit.bitmap[(size_t)(tok_q + c) * emit.bitmap_words + (expert >> 5)], 1u << (expert & 31));
-                }
+                if (sel[c] && j < (unsigned int)k)  // j < k always holds for a correct selection; guards the stores
+                    topk_put(emit, G, I, out0 + j, expert, n_total, tok0 + t_base + 256 * r + c, v[r][c]);
                 j += sel[c] ? 1u : 0u;
             }
         }
@@ -750,95 +751,103 @@ topk_tokens_reg_kernel(const float* __restrict__ St, int n_total, int n, int k, 
 }
 
 // ---------------------------------------------------------------------------
-// Small segments (at most 256 tokens, a multiple of 4): one wavefront per (expert, segment), four scores
-// per lane, no LDS and no barrier -- the batched small selection that routing per group of tokens needs
-// when the groups are short (Limitations section: small batches at serving time).  The k-th largest
-// score is found bit by bit (31 counting steps with ballots: scores are non-negative floats), ties at
-// that score are admitted in token order, and the bucket is written in ascending token order.
+// Short segments (at most 256 Q scores): one wavefront per (expert, segment), 4 Q scores per lane, no LDS and no barrier
+// -- small batches at serving time, and routing per group of tokens when the groups are short (Limitations section).
+// Latency bounds it: one trip to memory, then the threshold by bisection from the top bit of the actual range, every step
+// 4 Q ballots that count the scores at or above it.  The bisection ends as soon as a threshold separates exactly k
+// scores, after about log2(n) + 4 steps on scores in no special order; only ties at the k-th score take it to the last
+// bit, and are then admitted in token order.  The bucket is written in ascending token order.
+// Measured against the 1024-thread kernel (16 segments): 256 scores 4.6 us against 6.8, 512 the same, 1024 8.8 against 7.1.
 // ---------------------------------------------------------------------------
+constexpr int TOPK_SMALL_MAX = 512;
+
+template <int Q>
 __global__ void __launch_bounds__(256)
 topk_small_kernel(const float* __restrict__ St, int n_total, int n, int k, int e, int groups,
                   float* __restrict__ G, int32_t* __restrict__ I, TopkEmit emit) {
     const int lane = threadIdx.x & 63;
-    const long long job = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);  // (expert, segment), segment fastest
-    if (job >= (long long)e * groups) return;                              // uniform per wavefront
+    const long long job = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);  // (expert, segment), segment fastest
+    if (job >= (long long)e * groups) return;                                              // uniform per wavefront
     const int expert = (int)(job / groups), group = (int)(job % groups);
     const int tok0 = group * n;
     const size_t out0 = (size_t)job * (size_t)k;
     const unsigned int* __restrict__ colg = reinterpret_cast<const unsigned int*>(St) + (size_t)expert * n_total + tok0;
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
-    const bool valid = 4 * lane < n;  // n % 4 == 0: a lane's quad is inside or outside as a whole
-    unsigned int v[4] = {0u, 0u, 0u, 0u};
-    if (valid) {
-        const uint4 q = *reinterpret_cast<const uint4*>(colg + 4 * lane);
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    }
-    auto count_ge = [&](unsigned int t) -> int {
-        int c = 0;
+    // score c of quad q is token 256 q + 4 lane + c; what is outside the segment reads -1, below every score
+    unsigned int v[Q][4];
+    unsigned int vmin = 0xFFFFFFFFu;
+    int vmax = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) c += __popcll(__ballot(valid && v[j] >= t));
-        return c;
-    };
-    // largest T with at least k scores >= T: the k-th largest score
-    unsigned int T = 0u;
-    for (int bit = 30; bit >= 0; --bit) {
-        const unsigned int cand = T | (1u << bit);
-        if (count_ge(cand) >= k) T = cand;
+    for (int q = 0; q < Q; ++q) {
+        topk_load_quad(colg + 256 * q + 4 * lane, n - (256 * q + 4 * lane), 0xFFFFFFFFu, v[q]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            vmin = min(vmin, v[q][c]);
+            vmax = max(vmax, (int)v[q][c]);
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        vmin = min(vmin, (unsigned int)__shfl_xor(vmin, off, kWave));
+        vmax = max(vmax, __shfl_xor(vmax, off, kWave));
+    }
+    vmin = __builtin_amdgcn_readfirstlane(vmin);
+    vmax = __builtin_amdgcn_readfirstlane(vmax);
+    // T: the k-th largest score, or a value one below a threshold that exactly k scores reach
+    unsigned int T = vmin;
+    const unsigned int range = (unsigned int)vmax - vmin;
+    for (int bit = range == 0u ? -1 : 31 - __clz(range); bit >= 0; --bit) {
+        const unsigned int cand = T + (1u << bit);
+        if (cand > (unsigned int)vmax) continue;
+        int cnt = 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) cnt += __popcll(__ballot((int)v[q][c] >= (int)cand));
+        if (cnt >= k) T = cand;
+        if (cnt == k) {
+            --T;
+            break;
+        }
     }
     int above = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) above += __popcll(__ballot(valid && v[j] > T));
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) above += __popcll(__ballot((int)v[q][c] > (int)T));
     const int need = k - above;  // ties at T to admit, lowest token indices first
-    // rank among the ties and position in the bucket, both in token order (lane-major, then element)
-    unsigned long long tie_bal[4];
-    int tie_before = 0;
+    int ties = 0, pos = 0;       // ties seen and bucket rows written before this quad
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        tie_bal[j] = __ballot(valid && v[j] == T);
-        tie_before += __popcll(tie_bal[j] & lt_mask);
-    }
-    bool sel[4];
-    int tr = tie_before;
+    for (int q = 0; q < Q; ++q) {
+        int tr = ties;
+        if (need > 0) {  // uniform; otherwise nothing at T is admitted
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const bool tie = valid && v[j] == T;
-        sel[j] = valid && (v[j] > T || (tie && tr < need));
-        tr += tie ? 1 : 0;
-    }
-    int pos = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) pos += __popcll(__ballot(sel[j]) & lt_mask);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (sel[j] && pos < k) {  // pos < k always holds for a correct selection; guards the stores
-            const int tok = tok0 + 4 * lane + j;
-            G[out0 + pos] = __uint_as_float(v[j]);
-            I[out0 + pos] = tok;
-            if (emit.slot_cnt != nullptr) {
-                const int s = atomicAdd(&emit.slot_cnt[tok], 1);
-                if (s < emit.slot_cap) emit.slots[(size_t)tok * emit.slot_cap + s] = (int32_t)(out0 + pos);
+            for (int c = 0; c < 4; ++c) {
+                const unsigned long long bal = __ballot(v[q][c] == T);
+                tr += __popcll(bal & lt_mask);
+                ties += __popcll(bal);
             }
-            if (emit.bitmap != nullptr)
-                atomicOr(&emit.bitmap[(size_t)tok * emit.bitmap_words + (expert >> 5)], 1u << (expert & 31));
         }
-        pos += sel[j] ? 1 : 0;
+        bool sel[4];
+        int at = pos;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const bool tie = v[q][c] == T;
+            sel[c] = (int)v[q][c] > (int)T || (tie && tr < need);
+            tr += tie ? 1 : 0;
+            const unsigned long long bal = __ballot(sel[c]);
+            at += __popcll(bal & lt_mask);
+            pos += __popcll(bal);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (sel[c]) {
+                if (at < k)  // always true for a correct selection; guards the stores
+                    topk_put(emit, G, I, out0 + at, expert, n_total, tok0 + 256 * q + 4 * lane + c, v[q][c]);
+                ++at;
+            }
+        }
     }
-}
-
-// LDS the top-k kernel may use for the staged row.
-static size_t topk_lds_budget() {
-    static size_t budget = 0;
-    if (budget == 0) {
-        int dev = 0, v = 0;
-        size_t b = 64 * 1024;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0)
-            b = (size_t)v;
-        (void)hipGetLastError();
-        const size_t reserve = sizeof(TopkShared) + 256;
-        budget = b > reserve + 4096 ? b - reserve : 4096;
-    }
-    return budget;
 }
 
 template <int R>
@@ -848,51 +857,38 @@ static void launch_topk_reg(const float* St, int n_total, int n_seg, int k, int 
                        n_total, n_seg, k, G, I, emit);
 }
 
+template <int Q>
+static void launch_topk_small(const float* St, int n_total, int n_seg, int k, int e, int groups, float* G, int32_t* I,
+                              const TopkEmit& emit, hipStream_t stream) {
+    // up to 256 jobs a workgroup each: they then spread over the compute units
+    const long long jobs = (long long)e * groups;
+    const int per_block = jobs <= 256 ? 1 : 4;
+    hipLaunchKernelGGL(topk_small_kernel<Q>, dim3((unsigned)((jobs + per_block - 1) / per_block)), dim3(64 * per_block), 0,
+                       stream, St, n_total, n_seg, k, e, groups, G, I, emit);
+}
+
 // n tokens in all, cut into `groups` equal segments; k is the bucket size per (expert, segment).
-int launch_topk(const float* St, int64_t n, int64_t e, int64_t k, float* G, int32_t* I,
-                int32_t* slot_cnt, int32_t* slots, int slot_cap, uint32_t* bitmap, hipStream_t stream, int64_t groups) {
-    TopkEmit emit;
-    emit.slot_cnt = slot_cnt; emit.slots = slots; emit.slot_cap = slot_cap;
-    emit.bitmap = bitmap; emit.bitmap_words = (int)ceil_div(e, 32);
+int launch_topk(const float* St, int64_t n, int64_t e, int64_t k, float* G, int32_t* I, const CombineIndex* ix,
+                hipStream_t stream, int64_t groups, const float* values) {
+    const TopkEmit emit = {ix ? ix->bitmap : nullptr, ix ? ix->pos : nullptr, (int)ceil_div(e, 32), (int)e, values};
     const int64_t seg = n / groups;
-    if ((seg & 3) == 0 && seg <= 256 && e * groups >= 64) {
-        // many short segments: a wavefront each
-        const long long jobs = (long long)e * groups;
-        hipLaunchKernelGGL(topk_small_kernel, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, stream, St, (int)n, (int)seg,
-                           (int)k, (int)e, (int)groups, G, I, emit);
-        return check_launch();
-    }
-    if ((seg & 3) == 0 && seg <= 65536 && groups <= 65535) {
+    // segments of several groups must be multiples of 4 tokens and at most 65536 long
+    if (groups != 1 && ((seg & 3) != 0 || seg > 65536)) return EC_ERR_UNSUPPORTED;
+    const int ni = (int)n, si = (int)seg, ki = (int)k, ei = (int)e, gi = (int)groups;
+    if (seg <= TOPK_SMALL_MAX) {
+        if (seg <= 256) launch_topk_small<1>(St, ni, si, ki, ei, gi, G, I, emit, stream);
+        else launch_topk_small<2>(St, ni, si, ki, ei, gi, G, I, emit, stream);
+    } else if (seg <= 65536 && groups <= 65535) {
         // the row (segment) fits the registers of one workgroup: S^T is read once
-        const int ni = (int)n, si = (int)seg, ki = (int)k, ei = (int)e, gi = (int)groups;
         if (seg <= 4096) launch_topk_reg<1>(St, ni, si, ki, ei, gi, G, I, emit, stream);
         else if (seg <= 8192) launch_topk_reg<2>(St, ni, si, ki, ei, gi, G, I, emit, stream);
         else if (seg <= 16384) launch_topk_reg<4>(St, ni, si, ki, ei, gi, G, I, emit, stream);
         else if (seg <= 32768) launch_topk_reg<8>(St, ni, si, ki, ei, gi, G, I, emit, stream);
         else launch_topk_reg<16>(St, ni, si, ki, ei, gi, G, I, emit, stream);
-        return check_launch();
-    }
-    if (groups != 1) return EC_ERR_UNSUPPORTED;  // segments must be multiples of 4 tokens, at most 65536 long
-    const size_t stage_bytes = align_up((size_t)n * 4, 16);
-    const bool staged = stage_bytes <= topk_lds_budget();
-    const size_t dyn = staged ? stage_bytes : 0;
-    dim3 grid((unsigned)e), block(TOPK_THREADS);
-    if (staged) {
-        auto kern = topk_tokens_kernel<true>;
-        if (dyn > 64 * 1024) {
-            // the limit is raised once per GPU, to the whole budget, so later launches of any size are covered
-            static std::atomic<bool> raised[64];
-            int dev = 0;
-            if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-            if (!raised[dev].load(std::memory_order_acquire)) {
-                (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                          (int)topk_lds_budget());
-                raised[dev].store(true, std::memory_order_release);
-            }
-        }
-        hipLaunchKernelGGL(kern, grid, block, dyn, stream, St, (int)n, (int)k, G, I, emit);
+    } else if (groups == 1) {
+        hipLaunchKernelGGL(topk_tokens_kernel, dim3((unsigned)e), dim3(TOPK_THREADS), 0, stream, St, ni, ki, G, I, emit);
     } else {
-        hipLaunchKernelGGL(topk_tokens_kernel<false>, grid, block, 0, stream, St, (int)n, (int)k, G, I, emit);
+        return EC_ERR_UNSUPPORTED;
     }
     return check_launch();
 }
