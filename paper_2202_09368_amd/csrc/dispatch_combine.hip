@@ -343,6 +343,13 @@ int launch_combine(const void* Xe, const float* G, const int32_t* I, void* Xout,
 // uses that address, never the array's name.
 int combine_static(const void* Xe, const float* G, const int32_t* I, void* Xout, int64_t n, int64_t d, int64_t e,
                    int64_t k, int dtype, hipStream_t stream) {
+    // The documented limit, stated in what earlier forms of the index took: sizes stay accepted or refused as they were.
+    // Up to 16 experts the dense form takes 4 n (1 + e) bytes and fits whenever the limit admits the call.
+    auto part = [](size_t words) { return align_up(words * 4, 256); };
+    const size_t cap = e <= 4 ? 4 : e <= 8 ? 8 : 16;
+    const size_t need = e <= 16 ? part((size_t)n) + part((size_t)n * cap)
+                                : part(1024) + part((size_t)combine_zero_words(n, e)) + part((size_t)n + 1) + part((size_t)e * k);
+    if (need > (size_t)EC_MOE_STATIC_SCRATCH_BYTES) return EC_ERR_UNSUPPORTED;
     constexpr int MAX_DEVICES = 64;
     static std::mutex mu;
     static unsigned char* scratch_ptr[MAX_DEVICES] = {};
@@ -377,7 +384,6 @@ int combine_static(const void* Xe, const float* G, const int32_t* I, void* Xout,
         ix.block_tot = reinterpret_cast<uint32_t*>(take(1024 * 4));
         ix.offsets = reinterpret_cast<int32_t*>(take((size_t)(n + 1) * 4));
         ix.inv = reinterpret_cast<int32_t*>(take((size_t)e * k * 4));
-        if (off > (size_t)EC_MOE_STATIC_SCRATCH_BYTES) return EC_ERR_UNSUPPORTED;
     }
     int rc = launch_combine_index(I, n, e, k, ix, stream);  // clears the counters / bitmap with a fill kernel first
     if (rc != EC_OK) return rc;

@@ -138,7 +138,7 @@ def test_invalid_arguments_are_rejected_on_the_host(m):
     assert cap(2.0, 1e-3, -1, P, 1 << 30) == INV
     assert cap(2.0, 1e-3, 10, P, 64) == WS
     assert m.ec_moe_capped_workspace_bytes(0, 4) == 0 and m.ec_moe_capped_workspace_bytes(64, 4) >= 2 * 64 * 4 * 8
-    # the combine without a workspace: same argument checks (its size limit needs a GPU: the array's address is looked up first)
+    # the combine without a workspace: same argument checks
     assert lib.ec_moe_combine_static(P, P, None, P, 8, 16, 2, 4, 1, None) == INV
     assert lib.ec_moe_combine_static(P, P, P, P, 8, 12, 2, 4, 1, None) == INV
     # the timed backward: a host pointer for the stage times is required; stage names
@@ -163,3 +163,12 @@ def test_the_header_is_plain_c(tmp_path):
     r = subprocess.run([gcc, "-std=c99", "-Wall", "-Wextra", "-pedantic", "-Werror", "-fsyntax-only",
                         "-I", os.path.join(ROOT, "include"), str(src)], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
+
+
+@pytest.mark.parametrize("e,words_per_token", [(4, 5), (5, 9), (16, 17), (17, 2), (64, 3)])
+def test_static_scratch_combine_keeps_its_limit(m, e, words_per_token):
+    # header: 4 n (1 + slots) bytes up to 16 experts, 4 n (ceil(e / 32) + 1) + 4 e k + 4096 (parts rounded up) above;
+    # the check comes before anything asks for a GPU
+    n = (8 << 20) // (4 * words_per_token) + 1
+    P = 4096
+    assert m.lib().ec_moe_combine_static(P, P, P, P, n, 16, e, 1, 1, None) == -4
