@@ -18,8 +18,7 @@ namespace ecmoe {
 
 // True when the matrix-core kernel covers the product (with rows gathered from a [gather_rows, K] matrix if asked).
 // The left operand is contraction-contiguous, the right one keeps k as its row index: past K (any multiple of 8) the
-// buffer range check hands out zero rows of the weights, and what the last stage reads past the end of a left row --
-// the next row, finite numbers -- multiplies those zeros.
+// buffer range check hands out zeros for both (the left operand's offsets are moved out of range for the last stage).
 static bool gemm_bf16_fast_ok(int64_t M, int64_t N, int64_t K, bool gather, int64_t gather_rows) {
     constexpr int64_t most = ((int64_t)1 << 32) - (1 << 20);  // bytes of a group's matrix: 32-bit unsigned offsets
     return (K % 8) == 0 && (N % 8) == 0 && M * K * 2 < most && (K + 128) * N * 2 < most && M * N < (int64_t)1 << 31 &&

@@ -232,6 +232,19 @@ gemm_bf16_kernel(const bf16_t* __restrict__ Aall, const bf16_t* __restrict__ Bal
         for (int r = 0; r < B_CHUNKS; ++r) *reinterpret_cast<u32x4*>(&base[b_lds[r]]) = breg[r];
     };
 
+    // The columns of the left operand past K (right operand in its [K][N] form only): they lie in the next row, which may
+    // hold infinities, so the right operand's zeros do not make them harmless.  A thread loads the same eight columns of
+    // every row, so its offsets move past the end of the buffer once, before stage k0 is requested; later stages are
+    // never consumed.
+    auto clip_left = [&](int k0) {
+        if (A_MC || B_KC || SPLIT != SPLIT_NONE || k0 + GEMM_BK <= K) return;
+        const unsigned int end = 2u * (unsigned)(gather != nullptr ? gather_rows : M) * (unsigned)K;
+        if (k0 + (tid & 7) * 8 >= K) {
+#pragma unroll
+            for (int r = 0; r < A_CHUNKS; ++r) a_voff[r] = end;
+        }
+    };
+
     // Fragment addresses (element offsets in a stage) for step 0, tile 0.
     const int a_frag = A_MC ? (half * 8 + (l16 >> 2)) * A_PITCH + wr * WM + ((lane >> 4) & 1) * 16 + (l16 & 3) * 4
                             : (wr * WM + col) * A_PITCH + half * 8;
@@ -325,16 +338,18 @@ gemm_bf16_kernel(const bf16_t* __restrict__ Aall, const bf16_t* __restrict__ Bal
     };
 
     // Loads past the last stage read zeros or in-range data of the same group: harmless, never consumed.
-    // a ragged K is legal only when both operands keep k as the row index; a two-part left operand doubles the stages
+    // a two-part operand doubles the stages
     const int nk = (SPLIT != SPLIT_NONE ? 2 : 1) * ((K + GEMM_BK - 1) / GEMM_BK);
     if (STAGES == 2) {
         // Both of the first two stages are requested at once (one trip to memory instead of two in a row): stage 0
         // into a second set of registers that only lives here, stage 1 into the set the loop works with.
         u32x4 areg0[A_CHUNKS], breg0[B_CHUNKS];
+        clip_left(0);
 #pragma unroll
         for (int r = 0; r < A_CHUNKS; ++r) areg0[r] = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, a_voff[r], 0, 0);
 #pragma unroll
         for (int r = 0; r < B_CHUNKS; ++r) breg0[r] = __builtin_amdgcn_raw_buffer_load_b128(rsrcB, b_voff[r], 0, 0);
+        clip_left(GEMM_BK);
         load_tiles(GEMM_BK);
 #pragma unroll
         for (int r = 0; r < A_CHUNKS; ++r) *reinterpret_cast<u32x4*>(&smem[a_lds[r]]) = areg0[r];
@@ -348,6 +363,7 @@ gemm_bf16_kernel(const bf16_t* __restrict__ Aall, const bf16_t* __restrict__ Bal
             bf16_t* other = smem + (cur ^ 1) * STAGE;
             // Registers hold stage kc+1: it goes to the other buffer (last read before the previous
             // barrier) while stage kc+2 is requested, all within the first steps.
+            clip_left((kc + 2) * GEMM_BK);
 #pragma unroll
             for (int s = 0; s + 1 < STEPS; ++s) step(s, stage, s + 1, other, (kc + 2) * GEMM_BK, true);
             __syncthreads();  // stage kc+1 is complete in `other`; nobody reads `stage` any more
@@ -356,10 +372,12 @@ gemm_bf16_kernel(const bf16_t* __restrict__ Aall, const bf16_t* __restrict__ Bal
         }
         __syncthreads();  // every wavefront is done with the tile buffers before the epilogue reuses them
     } else {
+        clip_left(0);
         load_tiles(0);
         for (int kc = 0; kc < nk; ++kc) {
             store_tiles(0);  // the buffer is free: every wavefront passed the barrier that ends the previous phase
             __syncthreads();
+            clip_left((kc + 1) * GEMM_BK);
             load_tiles((kc + 1) * GEMM_BK);
             read_frags(0, smem, 0);
             __builtin_amdgcn_sched_barrier(0);

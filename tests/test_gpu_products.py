@@ -33,6 +33,27 @@ def test_bf16_ragged_widths(m, ref, kw):  # noqa: F811
     _stagewise(m, ref, w, wl.make_inputs(w))
 
 
+@pytest.mark.parametrize("e,k,d,d_ff", [(2, 70, 8, 8), (3, 300, 136, 72), (2, 520, 520, 200), (16, 512, 520, 3080)])
+def test_bf16_ragged_widths_keep_rows_apart(m, e, k, d, d_ff):  # noqa: F811
+    """A row that holds infinities and NaN leaves the rows beside it what they are without it, bit for bit: the last
+    stage of a contraction that 64 does not divide must not multiply the next row's elements, even by zeros."""
+    gen = torch.Generator(device="cuda").manual_seed(e * k + d)
+    Xin = torch.randn(e, k, d, generator=gen, device="cuda").bfloat16()
+    W1 = (torch.randn(e, d, d_ff, generator=gen, device="cuda") * d ** -0.5).bfloat16()
+    W2 = (torch.randn(e, d_ff, d, generator=gen, device="cuda") * d_ff ** -0.5).bfloat16()
+    ws = m.alloc_workspace(e * k, d, e, k, d_ff, m.EC_BF16)
+    clean, marked = torch.empty_like(Xin), torch.empty_like(Xin)
+    m.ec_moe_expert_ffn(Xin, W1, W2, clean, m.EC_ACT_IDENTITY, ws)
+    rows = [1, k // 2, k - 1]
+    Xin[:, rows] = torch.tensor([float("inf"), float("-inf"), float("nan")], device="cuda").bfloat16()[:, None]
+    m.ec_moe_expert_ffn(Xin, W1, W2, marked, m.EC_ACT_IDENTITY, ws)
+    keep = torch.ones(k, dtype=torch.bool, device="cuda")
+    keep[rows] = False
+    assert torch.isfinite(clean).all()
+    assert torch.equal(clean[:, keep], marked[:, keep])
+    assert torch.isnan(marked[:, k - 1]).all()
+
+
 @pytest.mark.parametrize("dtype,n,d,e", [
     ("bf16", 33, 8, 1), ("bf16", 95, 136, 7), ("bf16", 1000, 704, 20), ("bf16", 257, 200, 40), ("bf16", 100, 129, 100),
     ("bf16", 70, 320, 250), ("bf16", 64, 64, 256), ("f32", 31, 5, 3), ("f32", 1000, 260, 33), ("f32", 130, 96, 64),
