@@ -142,9 +142,9 @@ int ec_moe_combine(const void* Xe, const float* G, const int32_t* I, void* Xout,
  * a static device array of EC_MOE_STATIC_SCRATCH_BYTES inside the library (one copy per GPU, held
  * until the process ends) instead of in `ws`.  Nothing is allocated or freed, no memset is enqueued
  * (the index is cleared by a fill kernel).
- * Limit: the index must fit the array -- e <= 16: 4*n*(1 + cap) bytes with cap = 4, 8 or 16 slots
- * (the smallest that holds e); e > 16: 4*n*ceil(e/32) + 4*(n+1) + 4*e*k + 4096 bytes, each part rounded up
- * to 256.  Larger problems return EC_ERR_UNSUPPORTED and enqueue nothing.
+ * Limit: these sizes must fit the array -- e <= 16: 4*n*(1 + cap) bytes with cap = 4, 8 or 16
+ * (the smallest that holds e; the index takes no more); e > 16: 4*n*ceil(e/32) + 4*(n+1) + 4*e*k +
+ * 4096 bytes, each part rounded up to 256.  Larger problems return EC_ERR_UNSUPPORTED and enqueue nothing.
  * All calls on one GPU share the array, which keeps the previous call's contents: calls that overlap
  * on one GPU (different streams, or threads without ordering) race; order them on one stream.
  * The array's device address is looked up at the first call on a GPU: make that call outside a capture. */

@@ -72,7 +72,7 @@ def test_grouped_topk_rejects_bad_groups(m):
 
 @pytest.mark.parametrize("base,kw,groups", [
     ("cfg1", dict(n=512, d=64, e=8, d_ff=128), 4),                     # fp32
-    ("cfg2", dict(n=4096, d=256, e=16, d_ff=512), 8),                  # bf16, slot lists in the combine
+    ("cfg2", dict(n=4096, d=256, e=16, d_ff=512), 8),                  # bf16, dense index in the combine
     ("cfg3", dict(n=4096, d=128, e=64, d_ff=256), 16),                 # bf16, CSR index in the combine
     ("cfg5", dict(n=8192, d=128, e=32), 4),                            # identity experts
     ("cfg2", dict(), 8),                                               # full size, as `bench.py --groups 8` runs it

@@ -270,7 +270,7 @@ def _layer_hilo(m, ref, w, inp):
 
 
 @pytest.mark.parametrize("name,kw", [
-    ("cfg2", dict(n=2048, d=256, e=8, d_ff=512, act=wl.ACT_RELU)),      # slot lists
+    ("cfg2", dict(n=2048, d=256, e=8, d_ff=512, act=wl.ACT_RELU)),      # 8 experts, dense index
     ("cfg3", dict(n=4096, d=128, e=64, d_ff=256)),                       # CSR lists
     ("cfg2", dict(n=1000, d=192, e=16, d_ff=320)),                       # ragged bucket rows (k = 125)
 ])

@@ -91,7 +91,7 @@ def test_dispatch_and_combine_with_empty_rows(m, ref):
 
 @pytest.mark.parametrize("base,kw,m_top,c", [
     ("cfg1", dict(n=512, d=64, e=8, d_ff=128), 2, 2.0),                 # fp32
-    ("cfg2", dict(n=4096, d=256, e=16, d_ff=512), 2, 2.0),              # bf16, fused gather, slot lists
+    ("cfg2", dict(n=4096, d=256, e=16, d_ff=512), 2, 2.0),              # bf16, fused gather, dense index
     ("cfg2", dict(n=4096, d=256, e=16, d_ff=512), 1, 1.0),
     ("cfg3", dict(n=4096, d=128, e=64, d_ff=256), 2, 2.0),              # bf16, CSR combine index
     ("cfg5", dict(n=8192, d=128, e=32), 2, 2.0),                        # identity experts, skewed tokens

@@ -3,8 +3,8 @@ static device array inside the library) against ec_moe_combine on the same input
 
 Both run the same kernels in the same order of additions, so X_out must be bit-identical.  Two calls
 in a row on one GPU, the second with a smaller input, check that what the first call left in the
-shared array does not leak into the second; both index forms (slot lists for e <= 16, bitmap + CSR
-above) and both storage types are covered, and a problem too large for the array is refused.
+shared array does not leak into the second; both storage types are covered, and a problem too large for
+the array is refused.  (Sizes whose dense index does not fit and that take lists: test_gpu_index.py.)
 """
 import numpy as np
 import pytest
@@ -40,9 +40,9 @@ def _both(n, e, k, d, bf16, seed):
 
 @pytest.mark.parametrize("bf16", [True, False])
 @pytest.mark.parametrize("first,second", [
-    ((4096, 64, 128, 256), (1000, 24, 60, 64)),     # bitmap + CSR index, then a smaller one
-    ((4096, 16, 512, 128), (512, 8, 128, 64)),      # slot lists (16 slots), then 8 slots
-    ((2048, 40, 100, 96), (2048, 4, 700, 96)),      # CSR, then slot lists on the same token count
+    ((4096, 64, 128, 256), (1000, 24, 60, 64)),     # 64 experts, then a smaller problem
+    ((4096, 16, 512, 128), (512, 8, 128, 64)),      # 16 experts, then 8
+    ((2048, 40, 100, 96), (2048, 4, 700, 96)),      # 40 experts, then 4 on the same token count
 ])
 def test_static_scratch_combine_matches_workspace_combine(first, second, bf16):
     for seed, (n, e, k, d) in enumerate((first, second)):
